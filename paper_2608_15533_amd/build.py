@@ -26,9 +26,12 @@ SOURCES = ["abi.cpp", "dl_gdn.hip", "dl_kda.hip", "dl_rwkv6.hip", "dl_linattn.hi
 
 # No packed-fp32 instructions; MFMA accumulators in ordinary VGPRs (the merge's MFMA
 # contraction accumulates into the state tile's own registers: AGPR accumulators would
-# add 64 registers per lane and halve the occupancy).
+# add 64 registers per lane and halve the occupancy).  The first 14 words of a kernel's
+# scalar arguments arrive in scalar registers (the step kernel's first loads need no
+# argument load).
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-                "-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+                "-mllvm", "-amdgpu-mfma-vgpr-form=1",
+                "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 
 
 def hipcc():
@@ -95,7 +98,7 @@ def build_c_example(verbose=False):
 
 
 if __name__ == "__main__":
-    # python -m paper_2608_15533_amd.build [--out DIR] [hipcc flags, e.g. -DDL_MFMA_MERGE=1]
+    # python -m paper_2608_15533_amd.build [--out DIR] [hipcc flags, e.g. -DDL_XCD_CHUNK=16]
     # With --out the library (and its objects) go to DIR instead of the package: a build
     # variant that DELTALOG_LIB=DIR/libdeltalog.so selects at load time.
     args = sys.argv[1:]

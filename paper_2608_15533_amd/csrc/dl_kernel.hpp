@@ -1,18 +1,27 @@
 // DeltaLog decode kernels for gfx950 (CDNA4, wave64).
 //
 // One workgroup owns one (slot, head) state: a dk x dv matrix (64 KiB at 128x128 fp32).
-// Thread layout: NCG = dv/4 column groups (one float4 column slice each) times
-// NRG = dk/RPT row groups; every thread keeps RPT rows x 4 columns of the state in
-// registers (rows rg, rg+NRG, ..., so one wave-wide float4 load covers whole
-// consecutive rows, 1 KiB contiguous).  RPT = 16, or 4 for 64 x 64 heads.  The state
-// is read from HBM exactly once per step and, when the step materialises (merge /
-// eager / flush), written back exactly once from the same registers -- the read, the
-// key-dimension reductions and the write never leave the workgroup.  Because one
-// workgroup owns all of a head's value columns, the replay coefficients are computed
-// once per (slot, head) and the shared log metadata (K_log[L], Lam_log[L], L) has a
-// single writer without any cross-workgroup finalisation (the ownership problem of
+// Thread layout: NCG = dv/4 column groups (one float4 column slice each) times NRG row
+// groups; every thread keeps RPT = dk/NRG rows x 4 columns of the state in registers (rows
+// rg, rg+NRG, ..., so one wave-wide float4 load covers whole consecutive rows, 1 KiB
+// contiguous).  The state is read from HBM exactly once per step and, when the step
+// materialises (merge / eager / flush), written back exactly once from the same registers
+// -- the read, the key-dimension reductions and the write never leave the workgroup.
+// Because one workgroup owns all of a head's value columns, the replay coefficients are
+// computed once per (slot, head) and the shared log metadata (K_log[L], Lam_log[L], L) has
+// a single writer without any cross-workgroup finalisation (the ownership problem of
 // Sec. 3.3).  The cumulative log-decay ell is not stored: it equals the newest snapshot
 // Lam_log[L-1], or 0 with an empty log.
+//
+// The kernel is bound by HBM at large launches and by the chain launch -> live length and
+// tile -> log entries -> sums -> store at small ones.  The layout depends on the head shape
+// and the log capacity only, not on the number of rows: a slot's results do not depend on
+// what else is in the batch.  256 threads up to 16 log entries; 128 x 128 heads with
+// longer logs take 512 threads (twice the entries per coefficient pass, half the log
+// values per thread).  us per step in a captured graph, 256 against 512 threads:
+//   GDN 64x32 heads   M = 16: 25.9 / 26.8      KDA 128x32 heads  M = 16: 53.2 / 53.6
+//   KDA 128x32 heads  M = 32: 67.9 / 59.7      KDA 64x32 heads   M = 64: 39.6 / 39.1
+//   RetNet 8x16 heads M = 64: 4.99 / 4.57      GLA 100x32, bf16 state, M = 64: 43.5 / 41.7
 //
 // Modes (one template per mode; the per-slot append/merge branch of Alg. 1 is taken
 // on the device from that slot's live length):
@@ -156,119 +165,6 @@ __device__ __forceinline__ float dl_exp(float x) { return __expf(x); }
 #ifndef DL_STATE_STORE_POLICY
 #define DL_STATE_STORE_POLICY (DL_NT_STATE ? 18 : -1)
 #endif
-// Log keys of the first coefficient pass / the first replay values of each row group
-// are loaded before the first barrier (1) or where they are used (0).
-#ifndef DL_PREFETCH_KEYS
-#define DL_PREFETCH_KEYS 1
-#endif
-#ifndef DL_PREFETCH_U
-#define DL_PREFETCH_U 1
-#endif
-// Per-key log snapshots of the first coefficient pass are loaded before the first
-// barrier (1) or right after it (0, fewer live registers).
-#ifndef DL_PREFETCH_PER_KEY
-#define DL_PREFETCH_PER_KEY 0
-#endif
-#ifndef DL_PREFETCH_PER_KEY_SMALL
-#define DL_PREFETCH_PER_KEY_SMALL 1
-#endif
-// ... and for a bf16 state, whose tile holds half the registers of an fp32 one.
-#ifndef DL_PREFETCH_PER_KEY_BF16_STATE
-#define DL_PREFETCH_PER_KEY_BF16_STATE 1
-#endif
-// Row order of the staged K~ chunk in LDS: key row r = c * RPL + x (run c of the
-// coefficient pass, element x of the run) is kept at row x * LPE + c (1), or at r (0).
-// The coefficient pass writes one entry of RPL consecutive rows per lane; in key order
-// the lanes of a wave would meet in a few LDS banks, in this order their rows differ by
-// the run index instead.  The contraction's reads of row rg + NRG j stay at offsets
-// that are constant per j.
-#ifndef DL_KT_ROW_ORDER
-#define DL_KT_ROW_ORDER 1
-#endif
-// Order of the per-row token vectors the coefficient pass reads (k, q and the per-key
-// log-decays) in LDS: row r = c * RPL + x (run c, element x) at position x * LPE + c (1),
-// or at r (0).  A coefficient pass reads element x of every run at once, RPL rows
-// apart: in row order the 16 lanes of an entry meet in a few banks, in this order they
-// read consecutive words.
-#ifndef DL_COEF_LDS_ORDER
-#define DL_COEF_LDS_ORDER 1
-#endif
-// Long logs.  The STEP and MERGE kernels come in two builds: one for a capacity of at
-// most one coefficient pass (C <= 16), and one for longer logs, chosen by the host from
-// the descriptor's merge interval.  Only the long build carries the machinery below, so
-// the registers and LDS of the short build stay as they are.
-//   DL_STAGE_CHUNKS        merge chunks of decayed log keys staged in LDS by the
-//                          coefficient passes themselves (same loads and exps); later
-//                          chunks are staged from global memory.
-//   DL_PREFETCH_NEXT_PASS  load the next coefficient pass's log keys (1: and snapshots;
-//                          2: keys only) while the current pass computes.
-//   DL_PREFETCH_NEXT_PASS_PER_KEY  the same for 128-row per-key heads with bf16
-//                          activations, where it fits in the 4-wave long build (off:
-//                          the second pass's loads already leave right behind the
-//                          first pass's, and it measured no gain).
-//   DL_U_EARLY             load the log values of the next merge chunk before
-//                          contracting the current one.
-#ifndef DL_STAGE_CHUNKS
-#define DL_STAGE_CHUNKS 2
-#endif
-#ifndef DL_PREFETCH_NEXT_PASS
-#define DL_PREFETCH_NEXT_PASS 1
-#endif
-#ifndef DL_PREFETCH_NEXT_PASS_PER_KEY
-#define DL_PREFETCH_NEXT_PASS_PER_KEY 0
-#endif
-//   DL_PREFETCH_U_LATER    load the first pair of the replay's later log values
-//                          (entries rg + 2 NRG and rg + 3 NRG) with the first two, before
-//                          the first barrier, instead of after the coefficient passes.
-//                          Long builds with per-key decay, bf16 activations, an fp32 state
-//                          and 8 row groups only (128-row heads, whose later values start
-//                          with the second pass); the other builds would spill or lose a
-//                          wave.
-#ifndef DL_PREFETCH_U_LATER
-#define DL_PREFETCH_U_LATER 1
-#endif
-#ifndef DL_U_EARLY
-#define DL_U_EARLY 1
-#endif
-//   DL_REPLAY_PAIRS        replay the log values past the first two per row group two
-//                          at a time, with both loads issued before either is used.
-#ifndef DL_REPLAY_PAIRS
-#define DL_REPLAY_PAIRS 1
-#endif
-// The merge's rank-(L+1) contraction (Eq. 6) on the matrix cores (1: fp32 MFMA, twice
-// the rate of plain fp32 FMAs) or on the vector ALUs (0).  See MfmaMerge below.
-// DL_MFMA_MERGE_64COL = 0 keeps 64-column heads, DL_MFMA_MERGE_BF16_STATE = 0 a bf16
-// state, on the VALU path.
-#ifndef DL_MFMA_MERGE
-#define DL_MFMA_MERGE 1
-#endif
-#ifndef DL_MFMA_MERGE_64COL
-#define DL_MFMA_MERGE_64COL 1
-#endif
-#ifndef DL_MFMA_MERGE_BF16_STATE
-#define DL_MFMA_MERGE_BF16_STATE 1
-#endif
-#ifndef DL_MFMA_DRAIN
-#define DL_MFMA_DRAIN 1
-#endif
-// LDS layout of the staged K~ chunk where the merge contracts on MFMA: row R starts at
-// R * S + (R / 16) * P floats (1, S and P per head shape), or at R * 20 (0; the VALU
-// contraction's float4 reads need it).  An LDS access by a wave is served 32 lanes at a
-// time over 32 banks.  The MFMA operand read has those 32 lanes on 16 or 32 different rows
-// at one entry; the staging write has them on 16 consecutive rows at two entries.  With
-// the padded layout both land in 32 different banks (with R * 20, the read met in 4 or 8).
-#ifndef DL_KT_PAD
-#define DL_KT_PAD 1
-#endif
-// Issue order of the log entries relative to the state tile (see the kernel).
-#ifndef DL_LOG_FIRST
-#define DL_LOG_FIRST 0
-#endif
-// Occupancy target (waves per SIMD) handed to the register allocator; 0 = compiler's choice.
-#ifndef DL_WAVES_PER_EU
-#define DL_WAVES_PER_EU 0
-#endif
-
 // The state tile of one (slot, head) is addressed through a buffer resource: the
 // head's base address lives in scalar registers, each lane keeps one 32-bit offset and
 // the row blocks differ by a scalar offset, so no per-row 64-bit addresses occupy
@@ -301,20 +197,13 @@ template <> struct StateQuad<float> {
                     __uint_as_float(v[3]));
   }
   __device__ __forceinline__ float4 get() const { return w; }
+  __device__ __forceinline__ void opaque() {}
   static __device__ __forceinline__ void store(__amdgpu_buffer_rsrc_t r, uint32_t voff,
                                                uint32_t soff, float4 v) {
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
     const u32x4 x = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z),
                      __float_as_uint(v.w)};
     __builtin_amdgcn_raw_buffer_store_b128(x, r, voff, soff, kStateStorePolicy);
-  }
-  // The materialised rows at the end of a kernel: the row registers are the store data
-  // and nothing writes them afterwards.
-  template <int N>
-  static __device__ __forceinline__ void store_rows(__amdgpu_buffer_rsrc_t r, uint32_t voff,
-                                                    uint32_t row_block, const float4 (&m)[N]) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) store(r, voff, j * row_block, m[j]);
   }
 };
 template <> struct StateQuad<uint16_t> {
@@ -323,6 +212,9 @@ template <> struct StateQuad<uint16_t> {
     const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, kStateCachePolicy);
     w = make_uint2(v[0], v[1]);
   }
+  // The compiler takes the words as changed here: it widens them again for a later use
+  // instead of keeping the widened row (twice the registers) live until then.
+  __device__ __forceinline__ void opaque() { asm volatile("" : "+v"(w.x), "+v"(w.y)); }
   __device__ __forceinline__ float4 get() const {
     return make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u),
                        __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u));
@@ -333,43 +225,7 @@ template <> struct StateQuad<uint16_t> {
     const u32x2 x = {bf16_rne(v.x) | (bf16_rne(v.y) << 16), bf16_rne(v.z) | (bf16_rne(v.w) << 16)};
     __builtin_amdgcn_raw_buffer_store_b64(x, r, voff, soff, kStateStorePolicy);
   }
-  // The materialised rows at the end of a kernel.
-  template <int N>
-  static __device__ __forceinline__ void store_rows(__amdgpu_buffer_rsrc_t r, uint32_t voff,
-                                                    uint32_t row_block, const float4 (&m)[N]) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) store(r, voff, j * row_block, m[j]);
-  }
 };
-
-// N consecutive elements (N a multiple of 4) widened to fp32, loaded with 16-byte accesses
-// (8-byte accesses for bf16 runs whose length is not a multiple of 8).
-template <int N>
-__device__ __forceinline__ void ld_run(const float* p, float (&o)[N]) {
-#pragma unroll
-  for (int x = 0; x < N; x += 4) {
-    const float4 v = ld4(p + x);
-    o[x] = v.x; o[x + 1] = v.y; o[x + 2] = v.z; o[x + 3] = v.w;
-  }
-}
-template <int N>
-__device__ __forceinline__ void ld_run(const uint16_t* p, float (&o)[N]) {
-  static_assert(N % 4 == 0, "run length");
-  if constexpr (N % 8 != 0) {
-#pragma unroll
-    for (int x = 0; x < N; x += 4) {
-      const uint2 w = *reinterpret_cast<const uint2*>(p + x);
-      o[x + 0] = bf_lo(w.x); o[x + 1] = bf_hi(w.x); o[x + 2] = bf_lo(w.y); o[x + 3] = bf_hi(w.y);
-    }
-    return;
-  }
-#pragma unroll
-  for (int x = 0; x < N; x += 8) {
-    const uint4 w = *reinterpret_cast<const uint4*>(p + x);
-    o[x + 0] = bf_lo(w.x); o[x + 1] = bf_hi(w.x); o[x + 2] = bf_lo(w.y); o[x + 3] = bf_hi(w.y);
-    o[x + 4] = bf_lo(w.z); o[x + 5] = bf_hi(w.z); o[x + 6] = bf_lo(w.w); o[x + 7] = bf_hi(w.w);
-  }
-}
 
 constexpr uint32_t kXcds = 8;   // accelerator complex dies of an MI355X
 // (row, head) pairs per XCD chunk: 32 heads' 4-byte metadata is one 128-byte line.
@@ -406,11 +262,9 @@ template <int N> struct RawRun<float, N> {
 #pragma unroll
     for (int i = 0; i < N / 4; ++i) w[i] = reinterpret_cast<const float4*>(p)[i];
   }
-  __device__ __forceinline__ void get(float (&o)[N]) const {
-#pragma unroll
-    for (int i = 0; i < N / 4; ++i) {
-      o[4 * i] = w[i].x; o[4 * i + 1] = w[i].y; o[4 * i + 2] = w[i].z; o[4 * i + 3] = w[i].w;
-    }
+  __device__ __forceinline__ float at(int x) const {   // x a compile-time constant
+    const float4 v = w[x / 4];
+    return x % 4 == 0 ? v.x : x % 4 == 1 ? v.y : x % 4 == 2 ? v.z : v.w;
   }
 };
 template <int N> struct RawRun<uint16_t, N> {
@@ -422,22 +276,17 @@ template <int N> struct RawRun<uint16_t, N> {
 #pragma unroll
     for (int i = 0; i < (W16 ? N / 8 : N / 4); ++i) w[i] = reinterpret_cast<const Word*>(p)[i];
   }
-  __device__ __forceinline__ void get(float (&o)[N]) const {
+  __device__ __forceinline__ float at(int x) const {   // x a compile-time constant
+    uint32_t d;
     if constexpr (W16) {
-#pragma unroll
-      for (int i = 0; i < N / 8; ++i) {
-        o[8 * i + 0] = bf_lo(w[i].x); o[8 * i + 1] = bf_hi(w[i].x);
-        o[8 * i + 2] = bf_lo(w[i].y); o[8 * i + 3] = bf_hi(w[i].y);
-        o[8 * i + 4] = bf_lo(w[i].z); o[8 * i + 5] = bf_hi(w[i].z);
-        o[8 * i + 6] = bf_lo(w[i].w); o[8 * i + 7] = bf_hi(w[i].w);
-      }
+      const uint4 v = w[x / 8];
+      const int y = x % 8 / 2;
+      d = y == 0 ? v.x : y == 1 ? v.y : y == 2 ? v.z : v.w;
     } else {
-#pragma unroll
-      for (int i = 0; i < N / 4; ++i) {
-        o[4 * i + 0] = bf_lo(w[i].x); o[4 * i + 1] = bf_hi(w[i].x);
-        o[4 * i + 2] = bf_lo(w[i].y); o[4 * i + 3] = bf_hi(w[i].y);
-      }
+      const uint2 v = w[x / 4];
+      d = x % 4 / 2 == 0 ? v.x : v.y;
     }
+    return x % 2 ? bf_hi(d) : bf_lo(d);
   }
 };
 
@@ -468,18 +317,14 @@ __device__ __forceinline__ float scalar_ld(const float* ptr) {
 // Nothing may be scheduled across this point (loads keep their issue order).
 __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 
-// ------------------------------------------------------------------ configuration
-// Threads per workgroup for a dk x dv head: dv/4 column groups x dk/rows-per-thread
-// row groups.  Small (64 x 64) heads keep 4 rows per thread (four waves per head: short
-// per-thread chains for a 16 KiB state), the others 16 rows per thread.
-#ifndef DL_SMALL_HEAD_RPT
-#define DL_SMALL_HEAD_RPT 4
-#endif
-constexpr int rows_per_thread(int dk, int dv) {
-  return (dk == 64 && dv == 64) ? DL_SMALL_HEAD_RPT : 16;
+// The value is recomputed or re-read from here on, not kept: an empty asm block that
+// claims to change it.  Bounds how far the compiler moves the sums it feeds.
+__device__ __forceinline__ void pin(float& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void pin(float4& v) {
+  asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
 }
-constexpr int threads_per_head(int dk, int dv) { return (dv / 4) * (dk / rows_per_thread(dk, dv)); }
 
+// ------------------------------------------------------------------ configuration
 // What distinguishes the operators of Table 1 inside the kernel.
 template <int OP>
 struct OpTraits {
@@ -489,39 +334,36 @@ struct OpTraits {
   static constexpr bool BONUS = OP == OP_RWKV6;   // pre-update readout plus r^T diag(u) k v^T
 };
 
-template <int OP, int DK, int DV, int MODE, bool LONG = false>
+// U_log holds the delta rule's corrected values in fp32, and exact copies of v (in the
+// activation dtype) for every other operator.
+template <int OP, typename TIN>
+struct UType { using type = std::conditional_t<OpTraits<OP>::DELTA, float, TIN>; };
+
+// Log capacities the kernel is built for (CE entries; the host takes the smallest that
+// holds C = M - 1).  The log entries of a build are replayed from registers, loaded in one
+// go, so a longer log takes more registers and its own build.
+constexpr int log_build(int capacity) { return capacity <= 16 ? 16 : capacity <= 32 ? 32 : 64; }
+
+// Threads per workgroup.
+constexpr int threads_per_head(int dk, int dv, int ce) {
+  return dk == 128 && dv == 128 && ce > 16 ? 512 : 256;
+}
+
+template <int OP, int DK, int DV, int MODE, int CE_>
 struct Cfg {
-  static constexpr int RPT = rows_per_thread(DK, DV);   // state rows held per thread
+  static constexpr int CE = CE_;                 // log entries of the build (C <= CE)
+  static constexpr int NT = threads_per_head(DK, DV, CE);
   static constexpr int NCG = DV / 4;             // float4 column groups
-  static constexpr int NRG = DK / RPT;           // row groups
-  static constexpr int NT = NCG * NRG;           // threads per workgroup
-  static constexpr int NW = NT / 64;             // waves per workgroup
+  static constexpr int NRG = NT / NCG;           // row groups
+  static constexpr int RPT = DK / NRG;           // state rows per thread
+  static constexpr int NW = NT / 64;             // waves
   static constexpr int DL = OpTraits<OP>::PER_KEY ? DK : 1;   // log-decay width
-  static constexpr int EPP = 16;                 // log entries per coefficient pass
-  static constexpr int LPE = NT / EPP;           // lanes per log entry (coefficient pass)
+  static constexpr int LPE = DK == DV ? 16 : 8;  // lanes per log entry (coefficient pass)
   static constexpr int RPL = DK / LPE;           // key rows per lane (coefficient pass)
-  static constexpr int CH = 16;                  // log entries staged per merge chunk
-  static constexpr int KTS = CH + 4;             // LDS row stride, VALU layout
-  // Padded layout (row R at R * KT_S + (R / 16) * KT_P) for the MFMA contraction; the
-  // per-shape constants are the bank-conflict-free ones for its reads and the staging
-  // writes (a 64 x 128 or 128 x 64 head keeps a 2-way conflict on the read).
-  static constexpr bool KT_PADDED = DL_KT_PAD && DL_MFMA_MERGE &&
-                                    (DV / 4 == 32 || DL_MFMA_MERGE_64COL) && DL_MFMA_MERGE_BF16_STATE;
-  static constexpr int KT_S = !KT_PADDED ? KTS : DK == DV ? 18 : 20;
-  static constexpr int KT_P = !KT_PADDED ? 0 : DV / 4 == 32 ? 1 : 2;
-  static constexpr int kt_base_c(int r) { return r * KT_S + (r / 16) * KT_P; }
-  static constexpr int KT_CHUNK = (kt_base_c(DK) + 3) / 4 * 4;   // floats per staged chunk
-  // K~ chunks staged by the coefficient passes.  With per-key decay the long build keeps
-  // one: the second chunk's staging slows every append (measured), and the merge stages
-  // the later chunks itself, one chunk ahead.
-  static constexpr int NSTAGE = (LONG && !OpTraits<OP>::PER_KEY) ? DL_STAGE_CHUNKS : 1;
-  static constexpr bool U_EARLY = LONG && DL_U_EARLY;      // (fp32 state only: see kernel)
-  // The short build of STEP and MERGE only runs with a capacity of at most one pass
-  // (C <= CH); the other modes run with any capacity.
-  static constexpr bool CAP_ONE_PASS = (MODE == M_STEP || MODE == M_MERGE) && !LONG;
-  // A row group sees a second live entry (row group rg replays rg, rg + NRG, ...).
-  static constexpr bool TWO_PER_GROUP = !(CAP_ONE_PASS && NRG >= CH);
-  static constexpr int UPT = CH * NCG / NT;     // log-value quads per thread and merge chunk
+  static constexpr int EPP = NT / LPE < CE ? NT / LPE : CE;   // log entries per pass
+  static constexpr int NP = CE / EPP;            // coefficient passes
+  static constexpr int UQ = (CE + NRG - 1) / NRG;             // log-value quads per thread
+  static constexpr int KTS = CE + 4;             // LDS row stride of the decayed log keys
   static constexpr bool DELTA = OpTraits<OP>::DELTA;
   static constexpr bool DECAY = OpTraits<OP>::DECAY;
   static constexpr bool BONUS = OpTraits<OP>::BONUS;
@@ -532,278 +374,76 @@ struct Cfg {
   static constexpr bool CAN_MERGE = MODE != M_READOUT;
   static constexpr bool MERGES_LOG = CAN_MERGE && HAS_LOG;
   static constexpr bool REPLAYS = HAS_LOG && READS_OUT;   // readout of the live log
-  static_assert(NT % 64 == 0 && NT <= 256, "workgroup must be whole waves");
-  static_assert(64 % NCG == 0, "a wave must hold whole rows");
-  static_assert(NT % LPE == 0 && DK % LPE == 0, "coefficient pass layout");
-  static_assert(NT >= DK, "one thread per key row in the prologue");
-  static_assert(RPL == 4 || RPL == 8 || RPL == 16, "coefficient pass run length");
-  static_assert(NRG % RPL == 0 || RPL % NRG == 0, "row groups and coefficient runs nest");
-  static_assert(CH == EPP, "merge chunk c is staged by coefficient pass c");
-  static_assert(CH * NCG % NT == 0 && UPT >= 1, "whole log-value quads per thread");
-  static_assert(NSTAGE >= 1 && NSTAGE <= 4, "staged merge chunks");
-  // LDS row of key row r in the staged K~ chunk (a permutation of [0, DK)), and the
-  // same for the two ways the kernel names a row: element x of coefficient run c, and
-  // row j of row group rg (rg + NRG j), written so that the part that depends on x or j
-  // is a compile-time constant.
-  static __device__ __forceinline__ int kt_row(int r) {
-    return DL_KT_ROW_ORDER ? (r % RPL) * LPE + r / RPL : r;
-  }
-  static __device__ __forceinline__ int kt_row_run(int c, int x) {
-    return DL_KT_ROW_ORDER ? x * LPE + c : c * RPL + x;
-  }
-  // LDS offset of row r of the staged chunk, and of element x of coefficient run c (with
-  // the row order above, c < LPE and LPE dividing 16 keep (x LPE + c) / 16 = x LPE / 16,
-  // so the part that depends on x is a compile-time constant).
-  static __device__ __forceinline__ int kt_base(int r) { return r * KT_S + (r >> 4) * KT_P; }
-  static __device__ __forceinline__ int kt_off_run(int c, int x) {
-    if constexpr (DL_KT_ROW_ORDER) return c * KT_S + (x * LPE * KT_S + ((x * LPE) >> 4) * KT_P);
-    else return kt_base(c * RPL + x);
-  }
-  // LDS position of token row r in the vectors the coefficient pass reads (the same
-  // permutation as the K~ rows).
-  static __device__ __forceinline__ int cp_pos(int r) {
-    return DL_COEF_LDS_ORDER ? (r % RPL) * LPE + r / RPL : r;
-  }
-  static __device__ __forceinline__ int cp_pos_run(int c, int x) {
-    return DL_COEF_LDS_ORDER ? x * LPE + c : c * RPL + x;
-  }
-  static __device__ __forceinline__ int cp_pos_group(int rg, int j) {
-    if constexpr (!DL_COEF_LDS_ORDER) return rg + NRG * j;
-    else return kt_row_group_order(rg, j);
-  }
-  static __device__ __forceinline__ int kt_row_group(int rg, int j) {
-    if constexpr (!DL_KT_ROW_ORDER) return rg + NRG * j;
-    else return kt_row_group_order(rg, j);
-  }
-  // (rg + NRG j) % RPL * LPE + (rg + NRG j) / RPL, with the part that depends on j a
-  // compile-time constant.
-  static __device__ __forceinline__ int kt_row_group_order(int rg, int j) {
-    if constexpr (NRG % RPL == 0) {
-      return (rg % RPL) * LPE + rg / RPL + (NRG / RPL) * j;
-    } else {
-      constexpr int q = RPL / NRG;                  // RPL is a multiple of NRG
-      return (rg + NRG * (j % q)) * LPE + j / q;
-    }
-  }
-  static_assert(LPE <= 16 && 16 % LPE == 0, "an entry's lanes share one 16-lane row");
-  static_assert(NT == threads_per_head(DK, DV), "launch bound must match the layout");
+  // Waves of the per-row and the per-column work.
+  static constexpr int WK = DK / 64, WV = DV / 64;
+  // LDS floats of the cross-wave partial sums, and of the staged log values, which take
+  // the same place once the sums are read.
+  static constexpr int LRED = READS_OUT ? NW * 2 * DV : 0;
+  static constexpr int LU = MERGES_LOG ? CE * DV : 0;
+  static constexpr int LSCR = LRED > LU ? LRED : LU;
+  // Registers over latency: the readout and coefficient loops are kept from running
+  // ahead of themselves (see pin), which fits 128 x 128 heads with long logs in three
+  // workgroups of 512 threads per CU.
+  static constexpr bool LEAN = NT == 512;
+  static_assert(NT % 64 == 0 && NT >= DK && NT >= DV, "a thread per key row and value column");
+  static_assert(DK % NRG == 0 && RPT % 4 == 0, "whole blocks of four rows per thread");
+  static_assert(64 % NCG == 0 && (NCG == 16 || NCG == 32), "a wave holds whole rows");
+  static_assert(NT % LPE == 0 && (RPL == 4 || RPL == 8 || RPL == 16), "coefficient runs");
+  static_assert(CE % EPP == 0 && EPP % (64 / LPE) == 0, "whole passes of whole waves");
   static_assert(!(BONUS && DL == 1), "the bonus readout is only defined with per-key decay");
+  // LDS position of key row r in the vectors the coefficient pass reads and in the
+  // decayed log keys: the pass reads element x of every lane's run of RPL rows at once, so
+  // row r = c * RPL + x is kept at x * LPE + c (consecutive words for an entry's lanes).
+  static __device__ __forceinline__ int pos(int r) { return (r % RPL) * LPE + r / RPL; }
 };
 
-// ------------------------------------------------------------ MFMA merge contraction
-// The merge adds sum_i K~_i U_i^T to the decayed tile (Eq. 6), a product of a dk x n and
-// an n x dv matrix for a chunk of n log entries.  The tile is held row-streamed: thread
-// (rg, cg) owns rows rg + NRG j (j < RPT) and columns 4 cg .. 4 cg + 3, one 16-byte load
-// or store per row.  An fp32 MFMA leaves each lane one output column and a fixed set of
-// output rows.  Both index maps of the product are free, so they are chosen to make the
-// MFMA's output fragment the thread's own tile registers, with no data movement:
-//   * output column n of block b (b < 4) is state column 4 n + b, so the four blocks of
-//     a lane hold the four columns of its quad;
-//   * output row m is the state row that the lane holding m owns, so a lane's output
-//     rows are its own rows rg + NRG j.
-// With 128 columns (NCG = 32) a wave owns two row groups, 32 rows, and the product is
-// v_mfma_f32_32x32x2f32: lane l = 32 h + n holds output rows 8 (k / 4) + 4 h + k % 4
-// (k < 16), i.e. row group 2 w + h, row j = k.  The A operand (K~) of lane (h, n) is entry
-// h of the K-step at the row whose output lane n owns; the B operand (U) is entry h at
-// column 4 n + b, i.e. component b of the U quad of column group n = cg.  With 64
-// columns (NCG = 16) a wave owns four row groups and the product is
-// v_mfma_f32_16x16x4f32 over RPT / 4 blocks of 16 rows: lane l = 16 g + n holds rows
-// 4 g + k of a block, i.e. row group 4 w + g, row j = 4 mb + k.  The accumulators must be
-// ordinary VGPRs (the build's -amdgpu-mfma-vgpr-form): AGPR accumulators would add the
-// tile's registers again.
-template <int NCG, int RPT>
-struct MfmaMerge {                                // unused: VALU contraction
-  static constexpr int KS = 2, NMB = 1;
-  static __device__ __forceinline__ int row_of(int, int, int, int) { return 0; }
-  __device__ __forceinline__ void from_rows(const float4*) {}
-  __device__ __forceinline__ void to_rows(float4*) const {}
-  __device__ __forceinline__ void step(const float*, float4) {}
-  __device__ __forceinline__ void drain() {}
-  __device__ __forceinline__ void store_rows(__amdgpu_buffer_rsrc_t, uint32_t, uint32_t) const {}
-};
-
-template <int RPT>
-struct MfmaMerge<32, RPT> {                       // v_mfma_f32_32x32x2f32
-  static_assert(RPT == 16, "a 32-row block is the two row groups of a wave");
-  using V = float __attribute__((ext_vector_type(16)));
-  static constexpr int KS = 2;                    // log entries per MFMA
-  static constexpr int NMB = 1;                   // row blocks per wave
-  V acc[4];
-  // State row of output row m of the wave's block (row group 2w + (m / 4) % 2, row
-  // 4 (m / 8) + m % 4 of it).
-  static __device__ __forceinline__ int row_of(int w, int /*mb*/, int m, int NRG) {
-    return 2 * w + (m / 4) % 2 + NRG * (4 * (m / 8) + m % 4);
-  }
-  __device__ __forceinline__ void from_rows(const float4* t) {
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      acc[0][j] = t[j].x; acc[1][j] = t[j].y; acc[2][j] = t[j].z; acc[3][j] = t[j].w;
-    }
-  }
-  __device__ __forceinline__ void to_rows(float4* t) const {
-#pragma unroll
-    for (int j = 0; j < 16; ++j) t[j] = make_float4(acc[0][j], acc[1][j], acc[2][j], acc[3][j]);
-  }
-  __device__ __forceinline__ void step(const float* a, float4 b) {
-    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0], b.x, acc[0], 0, 0, 0);
-    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0], b.y, acc[1], 0, 0, 0);
-    acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0], b.z, acc[2], 0, 0, 0);
-    acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0], b.w, acc[3], 0, 0, 0);
-  }
-  // The tile's rows from the accumulators (component b of row j of the lane's quad is
-  // register j of block b), one 16-byte store per row.  Every row is gathered into
-  // registers of its own, and all of them stay allocated until the last store has issued:
-  // gathered into one reused set of four registers, each row's registers were rewritten
-  // right behind its store, and on the GPU that store then wrote the next row's value in
-  // lanes 12-15 of each 16-lane row now and then.
-  __device__ __forceinline__ void store_rows(__amdgpu_buffer_rsrc_t r, uint32_t voff,
-                                             uint32_t row_block) const {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    u32x4 x[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      x[j] = u32x4{__float_as_uint(acc[0][j]), __float_as_uint(acc[1][j]),
-                   __float_as_uint(acc[2][j]), __float_as_uint(acc[3][j])};
-      asm volatile("" : "+v"(x[j]));
-    }
-#pragma unroll
-    for (int j = 0; j < 16; ++j)
-      __builtin_amdgcn_raw_buffer_store_b128(x[j], r, voff, j * row_block, kStateStorePolicy);
-#pragma unroll
-    for (int j = 0; j < 16; ++j) asm volatile("" ::"v"(x[j]));
-  }
-  // Wait states between the last MFMA and the first VALU read of its results, on top
-  // of those the compiler inserts.
-  __device__ __forceinline__ void drain() {
-#if DL_MFMA_DRAIN
-    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7"
-                 : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
-#endif
-  }
-};
-
-template <int RPT>
-struct MfmaMerge<16, RPT> {                       // v_mfma_f32_16x16x4f32 (64 columns)
-  static_assert(RPT % 4 == 0, "16-row blocks, four rows per lane");
-  using V = float __attribute__((ext_vector_type(4)));
-  static constexpr int KS = 4;                    // log entries per MFMA
-  static constexpr int NMB = RPT / 4;             // row blocks per wave
-  V acc[NMB][4];
-  // State row of output row m of block mb: a wave owns four row groups (4 w + m / 4),
-  // and lane (g, n) holds rows 4 g + k of the block, row j = 4 mb + k of its group.
-  static __device__ __forceinline__ int row_of(int w, int mb, int m, int NRG) {
-    return 4 * w + m / 4 + NRG * (4 * mb + m % 4);
-  }
-  __device__ __forceinline__ void from_rows(const float4* t) {
-#pragma unroll
-    for (int mb = 0; mb < NMB; ++mb)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float4 r = t[4 * mb + k];
-        acc[mb][0][k] = r.x; acc[mb][1][k] = r.y; acc[mb][2][k] = r.z; acc[mb][3][k] = r.w;
-      }
-  }
-  __device__ __forceinline__ void to_rows(float4* t) const {
-#pragma unroll
-    for (int mb = 0; mb < NMB; ++mb)
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        t[4 * mb + k] = make_float4(acc[mb][0][k], acc[mb][1][k], acc[mb][2][k], acc[mb][3][k]);
-  }
-  __device__ __forceinline__ void step(const float* a, float4 b) {
-#pragma unroll
-    for (int mb = 0; mb < NMB; ++mb) {
-      acc[mb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mb], b.x, acc[mb][0], 0, 0, 0);
-      acc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mb], b.y, acc[mb][1], 0, 0, 0);
-      acc[mb][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mb], b.z, acc[mb][2], 0, 0, 0);
-      acc[mb][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mb], b.w, acc[mb][3], 0, 0, 0);
-    }
-  }
-  // As for 128 columns: every row in registers of its own, held until the last store.
-  __device__ __forceinline__ void store_rows(__amdgpu_buffer_rsrc_t r, uint32_t voff,
-                                             uint32_t row_block) const {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    u32x4 x[RPT];
-#pragma unroll
-    for (int mb = 0; mb < NMB; ++mb)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int j = 4 * mb + k;
-        x[j] = u32x4{__float_as_uint(acc[mb][0][k]), __float_as_uint(acc[mb][1][k]),
-                     __float_as_uint(acc[mb][2][k]), __float_as_uint(acc[mb][3][k])};
-        asm volatile("" : "+v"(x[j]));
-      }
-#pragma unroll
-    for (int j = 0; j < RPT; ++j)
-      __builtin_amdgcn_raw_buffer_store_b128(x[j], r, voff, j * row_block, kStateStorePolicy);
-#pragma unroll
-    for (int j = 0; j < RPT; ++j) asm volatile("" ::"v"(x[j]));
-  }
-  __device__ __forceinline__ void drain() {
-#if DL_MFMA_DRAIN
-#pragma unroll
-    for (int mb = 0; mb < NMB; ++mb)
-      asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7"
-                   : "+v"(acc[mb][0]), "+v"(acc[mb][1]), "+v"(acc[mb][2]), "+v"(acc[mb][3]));
-#endif
-  }
-};
-
-// U_log holds the delta rule's corrected values in fp32, and exact copies of v (in the
-// activation dtype) for every other operator.
-template <int OP, typename TIN>
-struct UType { using type = std::conditional_t<OpTraits<OP>::DELTA, float, TIN>; };
-
-// Occupancy target (waves per SIMD) for the register allocator: DL_WAVES_PER_EU for every
-// kernel if set, else DL_SMALL_HEAD_WAVES for 64 x 64 heads (1 = no target).
-#ifndef DL_SMALL_HEAD_WAVES
-#define DL_SMALL_HEAD_WAVES 6
-#endif
-// The long build of 128^2 heads with bf16 activations is held to 4 waves per SIMD (128
-// registers), the occupancy its short build has.
-#ifndef DL_LONG_WAVES
-#define DL_LONG_WAVES 4
-#endif
-constexpr int waves_target(int dk, int dv, bool long_build, int in_bytes) {
-  return DL_WAVES_PER_EU > 0 ? DL_WAVES_PER_EU
-         : (dk == 64 && dv == 64) ? DL_SMALL_HEAD_WAVES
-         : (long_build && dk == 128 && dv == 128 && in_bytes == 2) ? DL_LONG_WAVES
-                                                                    : 1;
+// Waves per SIMD the register allocator aims at: 4 (128 registers), and for the 512
+// threads of 17 to 32 log entries 6 (80), or 8 (64) with a bf16 state and bf16
+// activations.  More than 32 entries take LDS for two workgroups of 512 threads per CU in
+// any case.
+constexpr int waves_target(int dk, int dv, int ce, int state_bytes, int in_bytes) {
+  return threads_per_head(dk, dv, ce) != 512 || ce > 32 ? 4
+         : state_bytes == 2 && in_bytes == 2 ? 8 : 6;
 }
-#define DL_OCCUPANCY \
-  __attribute__((amdgpu_waves_per_eu(waves_target(DK, DV, LONG, int(sizeof(TIN))))))
 
 // ------------------------------------------------------------------ the kernel
-// Every global load a workgroup needs is issued before its first barrier: the token
-// rows, the state tile, the first pass of log keys/snapshots and the first log values
-// of the replay; only the live length (and the slot id, for slot lists) precede them.
-template <int OP, int DK, int DV, int MODE, typename TIN, typename TS, bool LONG>
-__global__ __launch_bounds__(threads_per_head(DK, DV)) DL_OCCUPANCY
-void deltalog_kernel(KParams p) {
-  using CF = Cfg<OP, DK, DV, MODE, LONG>;
+// One workgroup per (token row, head).
+//
+// The leading arguments are scalars, not a struct, so that they arrive in scalar registers
+// with the wave (the build asks for 14 preloaded argument words): the first loads then
+// wait for no argument load.  The order of the loads is by what waits for them: the live
+// length, the token's key and query (the prologue), the tile, and, once the length is
+// back, the log entries; the pointers of the latter are read meanwhile.  Measured against
+// a struct argument with the token rows under a branch (GDN 128 x 128, M = 16, us per
+// step in a captured graph): 64 heads 4.97 -> 4.03, 256 heads 6.31 -> 5.26, 2048 heads
+// 27.6 -> 25.9; RWKV6 64 x 64 with a bf16 state, 5120 heads: 15.4 -> 13.3.
+template <int OP, int DK, int DV, int MODE, typename TIN, typename TS, int CE>
+__global__ __launch_bounds__(threads_per_head(DK, DV, CE))
+__attribute__((amdgpu_waves_per_eu(waves_target(DK, DV, CE, int(sizeof(TS)), int(sizeof(TIN))))))
+void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k_,
+                     const void* q_, int H, uint32_t h_magic, int n, int C, KParams p) {
+  using CF = Cfg<OP, DK, DV, MODE, CE>;
   using TU = typename UType<OP, TIN>::type;
   constexpr int NT = CF::NT, NCG = CF::NCG, NRG = CF::NRG, RPT = CF::RPT, DL = CF::DL;
-  constexpr int RPL = CF::RPL;
+  constexpr int RPL = CF::RPL, LPE = CF::LPE, EPP = CF::EPP, NP = CF::NP, UQ = CF::UQ;
+  constexpr int KTS = CF::KTS, NW = CF::NW, WK = CF::WK, WV = CF::WV;
+  constexpr int EW = 64 / LPE;                    // log entries per wave and pass
+  constexpr int GW = 64 / NCG;                    // row groups per wave
 
-  __shared__ float s_kf[DK];      // k (raw)
-  __shared__ float s_qf[DK];      // q or r (raw)
-  __shared__ float s_xk[DK];      // e^(l_r) k_r       (base correction vector)
-  __shared__ float s_xq[DK];      // e^(l_r) q_r       (base readout vector)
-  __shared__ float s_em[DK];      // e^(l'_r)          (materialisation row scale)
-  __shared__ float s_lr[DL];      // readout log-decay l
-  __shared__ float s_lm[DL];      // materialisation log-decay l'
-  __shared__ float s_gk[DL_MAX_MERGE_INTERVAL];
-  __shared__ float s_gq[DL_MAX_MERGE_INTERVAL];
-  __shared__ float s_red[CF::NW][2][DV];
-  __shared__ float s_dotw[CF::NW];
-  // K~ chunks [NSTAGE][KT_CHUNK]: staged by the coefficient passes where the kernel
-  // replays the log, else (flush) one chunk at a time from global memory
-  constexpr int kKtChunks = CF::REPLAYS ? CF::NSTAGE : 1;
-  __shared__ float s_kt[CF::MERGES_LOG ? kKtChunks * CF::KT_CHUNK : 1];
-  __shared__ float4 s_u[CF::MERGES_LOG ? CF::CH * NCG : 1];          // U chunk  [CH][NCG]
+  __shared__ float s_kf[DK], s_qf[DK];            // k, q (coefficient-pass order)
+  __shared__ float2 s_x[DK];                      // e^(l_r) (k_r, q_r)
+  __shared__ float s_em[DK];                      // e^(l'_r)
+  __shared__ float s_lr[DL], s_lm[DL];            // l, l' (coefficient-pass order)
+  __shared__ float s_gk[CE], s_gq[CE];            // replay coefficients
+  __shared__ float s_dotw[WK];
+  __shared__ __align__(16) float s_bv[DV];
+  __shared__ __align__(16) float s_scr[CF::LSCR];
+  __shared__ __align__(16) float s_kt[CF::MERGES_LOG ? DK * KTS : 1];   // decayed log keys
+  float* const s_red = s_scr;                     // [NW][2][DV] partial sums
+  float4* const s_u = reinterpret_cast<float4*>(s_scr);   // [CE][NCG] log values
 
   const int tid = threadIdx.x;
-  const int H = p.H;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   // Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2).  Map
   // them so that each XCD owns whole chunks of DL_XCD_CHUNK consecutive (row, head)
   // pairs: the 4-byte per-head metadata (L and the head-wise log-decay snapshots) and token
@@ -813,7 +453,7 @@ void deltalog_kernel(KParams p) {
   // together) is spread over all eight XCDs instead of loading one of them.  Rows past
   // the last whole round of chunks keep the hardware order.
   uint32_t lin = blockIdx.x;
-  const uint32_t nblk = gridDim.x;
+  const uint32_t nblk = uint32_t(n) * uint32_t(H);
   if constexpr (kXcdChunk > 0) {
     const uint32_t full = nblk - nblk % (kXcds * kXcdChunk);
     if (lin < full) {
@@ -823,159 +463,118 @@ void deltalog_kernel(KParams p) {
   } else if (nblk % kXcds == 0) {
     lin = (lin % kXcds) * (nblk / kXcds) + lin / kXcds;   // one contiguous range per XCD
   }
-  const int row = int(lin) / H;                   // token row
-  const int h = int(lin) - row * H;               // head
-  const int slot = p.slots ? p.slots[row] : row;
-  if (slot < 0 || slot >= p.B) {                  // uniform per workgroup
-    if (tid == 0 && p.err) atomicOr(p.err, 1);
-    return;
+  // Token row lin / H and head lin % H.  h_magic = floor((2^32 - 1) / H) gives the
+  // quotient or one less for any lin < 2^32.
+  int row = int(__umulhi(lin, h_magic));
+  int h = int(lin) - row * H;
+  if (h >= H) {
+    h -= H;
+    ++row;
+  }
+  int slot = row;                                 // no list: the host has checked n <= B
+  if (slots) {
+    slot = slots[row];
+    if (slot < 0 || slot >= p.B) {                // uniform per workgroup
+      if (tid == 0 && p.err) atomicOr(p.err, 1);
+      return;
+    }
   }
   const size_t sh = size_t(slot) * H + h;         // state (slot, head) index
   const size_t th = size_t(row) * H + h;          // token (row, head) index
-  const int C = p.C;
-  // The live length is read through the scalar path (its own wait counter); it is
-  // first used only after the tile loads below have been issued.
+
+  // ---- 1. loads ------------------------------------------------------------------------
   int L_raw = 0;
-  if constexpr (CF::HAS_LOG) L_raw = p.len[sh];
-
-  // Vector loads return in issue order, so a wait for one load is a wait for every
-  // load issued before it.  The issue order is therefore: the small token rows (needed
-  // first, by the prologue), then the 64 KiB state tile, then the log entries (needed
-  // after the first barrier, once the live length is known).  Compiler barriers keep
-  // that order.
-
-  // ---- 1. token row values (the prologue's inputs) ---------------------------------
-  const TIN* kin = static_cast<const TIN*>(p.k) + th * DK;
-  const TIN* qin = static_cast<const TIN*>(p.q) + th * DK;
-  const int cg = tid % NCG;
-  const int rg = tid / NCG;
-  const int r0 = tid;                              // this thread's key row in the prologue
-  // Every thread loads (threads past dk re-read the last row and ignore it): a load
-  // under a branch would need its value at the branch join, i.e. an early wait.
-  const int rl = r0 < DK ? r0 : DK - 1;
-  const int rd = (DL == 1) ? 0 : rl;
-  TIN k_raw = TIN(0), q_raw = TIN(0);
-  float lam = 0.f, ell = 0.f, uf = 0.f;
-  if constexpr (CF::HAS_TOKEN) {
-    k_raw = kin[rl];
-    if constexpr (CF::DECAY) lam = p.lam[th * DL + rd];
-    if constexpr (CF::BONUS) uf = p.u[size_t(h) * DK + rl];
-  }
-  if constexpr (CF::READS_OUT) q_raw = qin[rl];
-  Raw4<TIN> v_raw{};
-  float beta = 0.f;
-  if constexpr (CF::HAS_TOKEN) {
-    v_raw.load(static_cast<const TIN*>(p.v) + th * DV + 4 * cg);
-    if constexpr (CF::DELTA) beta = p.beta[th];
-  }
-  asm volatile("" ::: "memory");
+  if constexpr (CF::HAS_LOG) L_raw = len[sh];
+  // Every thread loads token elements (threads past the row repeat its last element): a
+  // load under a branch is waited for at the branch's end.
+  const int rl = min(tid, DK - 1), cl = min(tid, DV - 1);
+  TIN k_raw = TIN(0), q_raw = TIN(0), v_raw = TIN(0);
+  Raw4<TIN> v4_raw{};
+  float lam = 0.f, ell = 0.f, uf = 0.f, beta = 0.f;
+  if constexpr (CF::HAS_TOKEN) k_raw = (static_cast<const TIN*>(k_) + th * DK)[rl];
+  if constexpr (CF::READS_OUT) q_raw = (static_cast<const TIN*>(q_) + th * DK)[rl];
+  if constexpr (CF::HAS_TOKEN && CF::DECAY && DL != 1) lam = p.lam[th * DL + rl];
   sched_fence();
 
-  // ---- 2. the state tile and the log entries of the first pass ---------------------
-  // Default order: tile, then (once the live length is back) the log entries, so the
-  // tile never waits for the length.  DL_LOG_FIRST = 1 waits for the length first and
-  // issues the log entries ahead of the tile, so the coefficient pass does not wait
-  // for the tile.
-  TS* const Sh = static_cast<TS*>(p.S) + sh * size_t(DK) * DV;
+  const int cg = tid % NCG, rg = tid / NCG;
+  TS* const Sh = static_cast<TS*>(S_) + sh * size_t(DK) * DV;
   const auto srs = state_rsrc(Sh, DK * DV * sizeof(TS));
   const uint32_t toff = uint32_t(rg * DV + 4 * cg) * sizeof(TS);   // lane's byte offset in a row block
   constexpr uint32_t kRowBlock = NRG * DV * sizeof(TS);             // bytes from row j to row j+1 of a lane
   StateQuad<TS> t[RPT];
-  if constexpr (!DL_LOG_FIRST) {
 #pragma unroll
-    for (int j = 0; j < RPT; ++j) t[j].load(srs, toff, j * kRowBlock);
-    asm volatile("" ::: "memory");
-    sched_fence();
+  for (int j = 0; j < RPT; ++j) t[j].load(srs, toff, j * kRowBlock);
+  if constexpr (CF::HAS_TOKEN) {
+    if constexpr (CF::DECAY && DL == 1) lam = scalar_ld(p.lam + th);
+    if constexpr (CF::BONUS) uf = p.u[size_t(h) * DK + rl];
+    if constexpr (MODE == M_EAGER) v4_raw.load(static_cast<const TIN*>(p.v) + th * DV + 4 * cg);
+    else v_raw = (static_cast<const TIN*>(p.v) + th * DV)[cl];
+    if constexpr (CF::DELTA) beta = scalar_ld(p.beta + th);
   }
+  const size_t LS = DL == 1 ? size_t(H) : size_t(DL);          // as lam_log_stride
+  const TIN* Kb = nullptr;
+  const TU* Ub = nullptr;
+  float* Lb = nullptr;
+  if constexpr (CF::HAS_LOG) {
+    Kb = static_cast<const TIN*>(p.k_log) + sh * size_t(C) * DK;
+    Ub = static_cast<const TU*>(p.u_log) + sh * size_t(C) * DV;
+    if constexpr (CF::DECAY)                                   // as lam_log_base
+      Lb = p.lam_log + (DL == 1 ? size_t(slot) * size_t(C) * H + h : sh * size_t(C) * DL);
+    // The pointers' argument loads complete beside the live length's, not after it.
+    asm volatile("" ::"s"(Kb), "s"(Ub), "s"(Lb));
+  }
+  sched_fence();
 
-  int L = __builtin_amdgcn_readfirstlane(L_raw);
-  const bool bad_len = L < 0 || L > C;
-  if (bad_len) L = 0;                             // keeps every address below in bounds
-  if (bad_len) {
+  const int L = __builtin_amdgcn_readfirstlane(L_raw);
+  if (L < 0 || L > C) {                           // every address below is in bounds
     if (tid == 0 && p.err) atomicOr(p.err, 2);
     return;
   }
-
-  const TIN* Kb = static_cast<const TIN*>(p.k_log) + sh * size_t(C) * DK;
-  float* const Lw = CF::DECAY ? lam_log_base<DL>(p, slot, h) : nullptr;
-  const float* Lb = Lw;
-  const size_t LS = lam_log_stride<DL>(p);
-  const TU* Ub = static_cast<const TU*>(p.u_log) + sh * size_t(C) * DV;
-  // The cumulative log-decay is not stored: after an append it equals the newest
-  // snapshot (Eq. 5 writes both with the same value), after a merge it is 0 (Eq. 6
-  // resets it with L).  Entry L-1 is not written by this launch (an append writes entry
-  // L), so one value per head is read through the scalar path, without waiting for the
-  // tile in flight; per-key values are one vector load per row.
-  if constexpr (CF::HAS_LOG && CF::DECAY) {
-    if constexpr (DL == 1) ell = L > 0 ? scalar_ld(Lb + size_t(L - 1) * LS) : 0.f;
-    else ell = L > 0 ? Lb[size_t(L - 1) * LS + rd] : 0.f;
-  }
-  const int e_ = tid / CF::LPE;                   // coefficient pass: entry within the pass
-  const int c_ = tid % CF::LPE;                   //                   key-row run
-  // Per-key snapshots are prefetched only where the registers allow it (small heads, or
-  // a bf16 state).
-  constexpr bool kPrefetchPerKey = DL_PREFETCH_PER_KEY || (DL_PREFETCH_PER_KEY_SMALL && RPT <= 8) ||
-                                   (DL_PREFETCH_PER_KEY_BF16_STATE && sizeof(TS) == 2 && RPL <= 8);
-  float kr[RPL], lr_[(DL == 1) ? 1 : RPL];
-  RawRun<TIN, RPL> kr_raw{};
-  RawRun<float, (DL == 1) ? 8 : RPL> lr_raw{};      // per-key snapshots (unused for DL == 1)
-  float lr0 = 0.f;                                   // scalar snapshot (DL == 1)
-  // The prefetch loads are unconditional (a load under a per-lane condition makes the
-  // wait counters conservative, i.e. waits for the tile): lanes past the live length
-  // re-read entry L-1 (same cache lines), an empty log reads entry 0, and a log of
-  // capacity 0 reads the head's own state tile instead; such values are never used.
-  const int Lm1 = L > 0 ? L - 1 : 0;
-  const TIN* Kp = C > 0 ? Kb : reinterpret_cast<const TIN*>(Sh);
-  const float* Lp = C > 0 ? Lb : reinterpret_cast<const float*>(Sh);
-  const TU* Up = C > 0 ? Ub : reinterpret_cast<const TU*>(Sh);
-  if constexpr (CF::REPLAYS && DL_PREFETCH_KEYS && (DL == 1 || kPrefetchPerKey)) {
-    const int ek = min(e_, Lm1);
-    kr_raw.load(Kp + size_t(ek) * DK + c_ * RPL);
-    if constexpr (DL == 1) {
-      if constexpr (CF::DECAY) lr0 = Lp[size_t(ek) * LS];
-    } else {
-      lr_raw.load(Lp + size_t(ek) * DK + c_ * RPL);
-    }
-  }
-  Raw4<TU> up0_raw{}, up1_raw{};                     // first two replay values of this row group
-  // ... and, in the long build, the next two (re-reads of entry L-1 where they are past
-  // the live length; the replay gives those a zero coefficient).
-  constexpr bool kLaterEarly = LONG && DL > 1 && sizeof(TIN) == 2 && sizeof(TS) == 4 &&
-                               CF::REPLAYS && DL_PREFETCH_U && DL_PREFETCH_U_LATER &&
-                               DL_REPLAY_PAIRS && 2 * NRG == CF::CH;
-  Raw4<TU> up2_raw{}, up3_raw{};
-  if constexpr (CF::REPLAYS && DL_PREFETCH_U) {
-    up0_raw.load(Up + size_t(min(rg, Lm1)) * DV + 4 * cg);
-    if constexpr (CF::TWO_PER_GROUP) up1_raw.load(Up + size_t(min(rg + NRG, Lm1)) * DV + 4 * cg);
-    if constexpr (kLaterEarly) {
-      up2_raw.load(Up + size_t(min(rg + 2 * NRG, Lm1)) * DV + 4 * cg);
-      up3_raw.load(Up + size_t(min(rg + 3 * NRG, Lm1)) * DV + 4 * cg);
-    }
-  }
-  if constexpr (DL_LOG_FIRST) {
-    sched_fence();
+  // Log entries: lanes past the live length re-read entry L-1 (unused values); waves past
+  // it load nothing.
+  const int e_ = tid / LPE, c_ = tid % LPE;       // coefficient pass: entry, key-row run
+  const int ew = w * EW;                          // ... the wave's first entry
+  RawRun<TIN, RPL> kr_raw[NP];
+  RawRun<float, DL == 1 ? 4 : RPL> lr_raw[NP];    // per-key snapshots (unused for DL == 1)
+  float lr0[NP] = {};                             // scalar snapshots (DL == 1)
+  Raw4<TU> u_raw[UQ];
+  if constexpr (CF::REPLAYS) {
 #pragma unroll
-    for (int j = 0; j < RPT; ++j) t[j].load(srs, toff, j * kRowBlock);
+    for (int a = 0; a < NP; ++a) {
+      if (ew < EPP && a * EPP + ew < L) {         // uniform per wave
+        const int i = min(a * EPP + e_, L - 1);
+        kr_raw[a].load(Kb + size_t(i) * DK + c_ * RPL);
+        if constexpr (CF::DECAY) {
+          if constexpr (DL == 1) lr0[a] = Lb[size_t(i) * LS];
+          else lr_raw[a].load(Lb + size_t(i) * DK + c_ * RPL);
+        }
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < UQ; ++a)
+      if (a * NRG + w * GW < L)                   // uniform per wave
+        u_raw[a].load(Ub + size_t(min(a * NRG + rg, L - 1)) * DV + 4 * cg);
   }
   sched_fence();
-  const float kf = to_f32(k_raw), qf = to_f32(q_raw);
-
   // Does this (slot, head) materialise in this launch?  (Uniform per workgroup.)
   const bool merging = MODE == M_MERGE || MODE == M_FLUSH || MODE == M_EAGER ||
                        (MODE == M_STEP && L == C);
-  if constexpr (CF::MERGES_LOG) {
-    // The first chunk of log values is staged by the replay below; entries at or past L
-    // in that chunk must read as zero in the merge contraction.
-    if (merging)
-      for (int x = tid; x < CF::CH * NCG; x += NT)
-        if (x / NCG >= L) s_u[x] = f4(0.f);
-  }
 
-  // ---- 4. per-row decay factors (LDS) and the token dot product ---------------------
-  if (r0 < DK) {
-    float lr, lm;
+  // ---- 2. per-row decay factors (LDS) and the token dot product -----------------------
+  if (w < WK) {
+    // The cumulative log-decay equals the newest snapshot (Eq. 5 writes both with the
+    // same value) or 0 with an empty log.  Entry L-1 is not written by this launch, so
+    // one value per head is read through the scalar path.
+    if constexpr (CF::HAS_LOG && CF::DECAY) {
+      if (L > 0) {
+        if constexpr (DL == 1) ell = scalar_ld(Lb + size_t(L - 1) * LS);
+        else ell = Lb[size_t(L - 1) * LS + tid];
+      }
+    }
+    const float kf = to_f32(k_raw), qf = to_f32(q_raw);
     // Readouts of the decayed state (the delta-rule correction, and the post-update
     // output's base part), except RWKV6, which reads the old state.
+    float lr, lm;
     if constexpr (MODE == M_EAGER) {
       lr = CF::BONUS ? 0.f : lam;
       lm = lam;
@@ -987,458 +586,321 @@ void deltalog_kernel(KParams p) {
       lm = ell;
     }
     const float er = dl_exp(lr);
-    const int pr = CF::cp_pos(r0);                // coefficient-pass order
+    const int pr = CF::pos(tid);
     s_kf[pr] = kf;
     s_qf[pr] = qf;
-    s_xk[r0] = er * kf;
-    s_xq[r0] = er * qf;
-    s_em[r0] = dl_exp(lm);
-    if (r0 < DL) {                                // DL == 1: r0 == 0 == pr
+    s_x[tid] = make_float2(er * kf, er * qf);
+    s_em[tid] = dl_exp(lm);
+    if (tid < DL) {                               // DL == 1: tid == 0 == pr
       s_lr[pr] = lr;
       s_lm[pr] = lm;
     }
-  }
-  if constexpr (CF::HAS_TOKEN) {
-    // q.k (post-update readout of the new term) or r.(u*k) (RWKV6 bonus)
-    float d = CF::BONUS ? qf * uf * kf : qf * kf;
-    if (r0 >= DK) d = 0.f;                        // threads past dk hold a repeated row
-    d = xor32_sum(xor16_sum(group_sum<16>(d)));
-    if ((tid & 63) == 0) s_dotw[tid >> 6] = d;
+    if constexpr (CF::HAS_TOKEN) {
+      // q.k (post-update readout of the new term) or r.(u*k) (RWKV6 bonus)
+      float d = CF::BONUS ? qf * uf * kf : qf * kf;
+      d = xor32_sum(xor16_sum(group_sum<16>(d)));
+      if ((tid & 63) == 0) s_dotw[w] = d;
+    }
   }
   __syncthreads();
 
-  // ---- 5. replay coefficients g_i(k), g_i(q) of the live entries --------------------
-  // A merging workgroup also writes the decayed keys K~_i[r] = e^(l'_r - Lam_i,r) K_i[r]
-  // of the first NSTAGE chunks to LDS here, from the same loads and exps (the merge
-  // decay l' equals the readout decay, except for RWKV6, which reads at ell).  With
-  // DL_PREFETCH_NEXT_PASS the next pass's keys and snapshots are loaded before the
-  // current pass computes.
-  if constexpr (CF::REPLAYS) {
-    constexpr bool kFirstPrefetched = DL_PREFETCH_KEYS && (DL == 1 || kPrefetchPerKey);
-    // The next pass is prefetched where the registers allow it at the build's occupancy:
-    // one log-decay per head (a scalar snapshot) or small heads; optionally 128² per-key
-    // heads with bf16 activations (the 4-wave long build; the bonus readout's extra
-    // registers leave room for the keys only).  With fp32 activations or other shapes a
-    // 128-row per-key head would need 12 more registers across the pass (one wave less).
-    constexpr int kNextPerKey =
-        (sizeof(TIN) == 2 && DK == 128 && DV == 128 && DL_PREFETCH_NEXT_PASS_PER_KEY)
-            ? (CF::BONUS ? 2 : DL_PREFETCH_NEXT_PASS) : 0;
-    constexpr int kNext = !LONG ? 0 : (DL == 1 || RPT <= 8) ? DL_PREFETCH_NEXT_PASS : kNextPerKey;
-    RawRun<TIN, RPL> kn_raw{};
-    RawRun<float, (DL == 1) ? 8 : RPL> ln_raw{};
-    float ln0 = 0.f;
-    bool next_ready = false;                      // uniform
-    // The short STEP/MERGE build runs with C <= EPP: at most one pass, compiled as such.
-    const int passes_end = CF::CAP_ONE_PASS ? min(L, 1) : L;
-    for (int i0 = 0; i0 < passes_end; i0 += CF::EPP) {   // uniform trip count
-      const int i = i0 + e_;
-      const int chunk = i0 / CF::CH;
-      const bool stage = CF::MERGES_LOG && merging && chunk < kKtChunks;
-      float* const kt = s_kt + (stage ? chunk : 0) * CF::KT_CHUNK;
-      float ak = 0.f, aq = 0.f;
-      const bool from_next = next_ready;
-      const bool from_first = kFirstPrefetched && i0 == 0;
-      constexpr bool kNextSnap = kNext == 1;      // snapshots prefetched too
-      // This pass's own loads, issued together and unconditionally (lanes past the live
-      // length re-read entry L-1, unused): a load under a per-lane condition is waited
-      // for at the condition's end, which would serialise the key and snapshot round
-      // trips.
-      const bool keys_here = !from_next && !from_first;                   // uniform
-      const bool snaps_here = !from_first && !(from_next && kNextSnap);
-      const int ic = min(i, L - 1);
-      RawRun<TIN, RPL> kc_raw{};
-      RawRun<float, (DL == 1) ? 8 : RPL> lc_raw{};
-      float lc0 = 0.f;
-      if (keys_here) kc_raw.load(Kb + size_t(ic) * DK + c_ * RPL);
-      if (snaps_here) {
-        if constexpr (DL == 1) {
-          if constexpr (CF::DECAY) lc0 = Lb[size_t(ic) * LS];
-        } else {
-          lc_raw.load(Lb + size_t(ic) * DK + c_ * RPL);
-        }
-      }
-      if (keys_here) kc_raw.get(kr);
-      if (snaps_here) {
-        if constexpr (DL == 1) lr_[0] = lc0;
-        else lc_raw.get(lr_);
-      }
-      if (from_next) {
-        kn_raw.get(kr);
-        if constexpr (kNextSnap) {
-          if constexpr (DL == 1) lr_[0] = ln0;
-          else ln_raw.get(lr_);
-        }
-      } else if (from_first) {
-        kr_raw.get(kr);
-        if constexpr (DL == 1) lr_[0] = lr0;
-        else lr_raw.get(lr_);
-      }
-      next_ready = false;
-      if constexpr (kNext > 0) {
-        if (i0 + CF::EPP < L) {                   // uniform
-          const int en = min(i + CF::EPP, L - 1);
-          kn_raw.load(Kb + size_t(en) * DK + c_ * RPL);
-          if constexpr (kNextSnap) {
-            if constexpr (DL == 1) {
-              if constexpr (CF::DECAY) ln0 = Lb[size_t(en) * LS];
-            } else {
-              ln_raw.load(Lb + size_t(en) * DK + c_ * RPL);
-            }
-          }
-          next_ready = true;
-        }
-      }
-      if (i < L) {
-        if constexpr (DL == 1) {
-#pragma unroll
-          for (int x = 0; x < RPL; ++x) {
-            const int pr = CF::cp_pos_run(c_, x);
-            if constexpr (CF::NEEDS_C) ak = fmaf(kr[x], s_kf[pr], ak);
-            aq = fmaf(kr[x], s_qf[pr], aq);
-          }
-          const float w = CF::DECAY ? dl_exp(s_lr[0] - lr_[0]) : 1.f;
-          if constexpr (CF::NEEDS_C) ak *= w;
-          aq *= w;
-          if (stage) {
-#pragma unroll
-            for (int x = 0; x < RPL; ++x) {
-              kt[CF::kt_off_run(c_, x) + e_] = w * kr[x];
-            }
-          }
-        } else {
-#pragma unroll 2
-          for (int x = 0; x < RPL; ++x) {
-            const int pr = CF::cp_pos_run(c_, x);
-            const float wk = dl_exp(s_lr[pr] - lr_[x]) * kr[x];
-            if constexpr (CF::NEEDS_C) ak = fmaf(wk, s_kf[pr], ak);
-            aq = fmaf(wk, s_qf[pr], aq);
-            if (stage)
-              kt[CF::kt_off_run(c_, x) + e_] =
-                  CF::BONUS ? dl_exp(s_lm[pr] - lr_[x]) * kr[x] : wk;
-          }
-        }
-      } else if (stage) {
-#pragma unroll
-        for (int x = 0; x < RPL; ++x) {
-          kt[CF::kt_off_run(c_, x) + e_] = 0.f;
-        }
-      }
-      if constexpr (CF::NEEDS_C) ak = group_sum<CF::LPE>(ak);   // the delta-rule correction only
-      aq = group_sum<CF::LPE>(aq);
-      if (c_ == 0 && i < L) {
-        if constexpr (CF::NEEDS_C) s_gk[i] = ak;
-        s_gq[i] = aq;
-      }
-    }
-    __syncthreads();
-  }
-
-  // ---- 6. base readouts from the registers + log replay, reduced over rows -------
+  // ---- 3. base readout from the registers (the log entries may still be in flight) ------
   float4 cv = f4(0.f), ov = f4(0.f);
   if constexpr (CF::READS_OUT) {
 #pragma unroll
     for (int j = 0; j < RPT; ++j) {
-      const int r = rg + NRG * j;
+      const float2 x = s_x[rg + NRG * j];
       const float4 sj = t[j].get();
-      if constexpr (CF::NEEDS_C) cv = fma4(s_xk[r], sj, cv);
-      ov = fma4(s_xq[r], sj, ov);
+      if constexpr (CF::CAN_MERGE) t[j].opaque();
+      if constexpr (CF::NEEDS_C) cv = fma4(x.x, sj, cv);
+      ov = fma4(x.y, sj, ov);
+      if (CF::LEAN && j % 2 == 1) {
+        if constexpr (CF::NEEDS_C) pin(cv);
+        pin(ov);
+      }
     }
-    if constexpr (CF::HAS_LOG) {
-      // Each log value row is read by exactly one row group; a merging workgroup keeps
-      // the first chunk of them in LDS for the merge contraction.
-      const bool stage_u = CF::MERGES_LOG && merging;
-      const float4 up0 = up0_raw.get(), up1 = up1_raw.get();
-      if (DL_PREFETCH_U && rg < L) {
-        if constexpr (CF::NEEDS_C) cv = fma4(s_gk[rg], up0, cv);
-        ov = fma4(s_gq[rg], up0, ov);
-        if (stage_u && rg < CF::CH) s_u[rg * NCG + cg] = up0;
-      }
-      if (CF::TWO_PER_GROUP && DL_PREFETCH_U && rg + NRG < L) {
-        if constexpr (CF::NEEDS_C) cv = fma4(s_gk[rg + NRG], up1, cv);
-        ov = fma4(s_gq[rg + NRG], up1, ov);
-        if (stage_u && rg + NRG < CF::CH) s_u[(rg + NRG) * NCG + cg] = up1;
-      }
-      constexpr int kFirstLater = DL_PREFETCH_U ? 2 * NRG : 0;   // first entry replayed here
-      if constexpr (LONG && DL_REPLAY_PAIRS && kFirstLater >= CF::CH) {
-        // The later values two rows of entries at a time, on a loop bound that is uniform
-        // over the workgroup: both loads are issued before either is used.  Lanes past
-        // the live length re-read entry L-1 (a finite value) with a zero coefficient, so
-        // no load waits at the end of a per-lane condition.
-        if constexpr (kLaterEarly) {              // the pair loaded before the first barrier
-          if (kFirstLater < L) {
-            const int i0 = kFirstLater + rg, i1 = kFirstLater + NRG + rg;
-            const int j0 = min(i0, L - 1), j1 = min(i1, L - 1);
-            const float4 u0 = up2_raw.get();
-            if constexpr (CF::NEEDS_C) cv = fma4(i0 < L ? s_gk[j0] : 0.f, u0, cv);
-            ov = fma4(i0 < L ? s_gq[j0] : 0.f, u0, ov);
-            const float4 u1 = up3_raw.get();
-            if constexpr (CF::NEEDS_C) cv = fma4(i1 < L ? s_gk[j1] : 0.f, u1, cv);
-            ov = fma4(i1 < L ? s_gq[j1] : 0.f, u1, ov);
+    if constexpr (CF::NEEDS_C) pin(cv);
+    pin(ov);
+  }
+
+  // ---- 4. replay coefficients g_i(k), g_i(q) of the live entries ---------------------
+  // A merging workgroup also writes the decayed keys K~_i[r] = e^(l'_r - Lam_i,r) K_i[r]
+  // to LDS here, from the same loads (the merge decay l' equals the readout decay, except
+  // for RWKV6, which reads at ell), zeros past the live length.
+  if constexpr (CF::REPLAYS) {
+#pragma unroll
+    for (int a = 0; a < NP; ++a) {
+      const bool stage = CF::MERGES_LOG && merging;
+      if (ew < EPP && (a * EPP + ew < L || stage)) {          // uniform per wave
+        const int i = a * EPP + e_;
+        const bool live = i < L;
+        float ak = 0.f, aq = 0.f, wt = 1.f;
+        if constexpr (DL == 1 && CF::DECAY) wt = live ? dl_exp(s_lr[0] - lr0[a]) : 0.f;
+#pragma unroll
+        for (int x = 0; x < RPL; ++x) {
+          const int pr = x * LPE + c_;
+          float kx = kr_raw[a].at(x);
+          if constexpr (DL != 1) kx *= dl_exp(s_lr[pr] - lr_raw[a].at(x));
+          if constexpr (CF::NEEDS_C) ak = fmaf(kx, s_kf[pr], ak);
+          aq = fmaf(kx, s_qf[pr], aq);
+          if (DL != 1 && !CF::BONUS && stage) s_kt[pr * KTS + i] = live ? kx : 0.f;
+          if (CF::LEAN && x % 4 == 3) {
+            pin(ak);
+            pin(aq);
           }
         }
-        for (int base = kFirstLater + (kLaterEarly ? 2 * NRG : 0); base < L; base += 2 * NRG) {
-          const int i0 = base + rg, i1 = base + NRG + rg;
-          const int j0 = min(i0, L - 1), j1 = min(i1, L - 1);
-          Raw4<TU> r0, r1;                        // (bf16 values widened one at a time)
-          r0.load(Ub + size_t(j0) * DV + 4 * cg);
-          r1.load(Ub + size_t(j1) * DV + 4 * cg);
-          const float4 u0 = r0.get();
-          if constexpr (CF::NEEDS_C) cv = fma4(i0 < L ? s_gk[j0] : 0.f, u0, cv);
-          ov = fma4(i0 < L ? s_gq[j0] : 0.f, u0, ov);
-          const float4 u1 = r1.get();
-          if constexpr (CF::NEEDS_C) cv = fma4(i1 < L ? s_gk[j1] : 0.f, u1, cv);
-          ov = fma4(i1 < L ? s_gq[j1] : 0.f, u1, ov);
+        if constexpr (DL == 1 && CF::DECAY) {
+          if constexpr (CF::NEEDS_C) ak *= wt;
+          aq *= wt;
         }
-      } else if constexpr (!(CF::CAP_ONE_PASS && DL_PREFETCH_U && 2 * NRG >= CF::CH)) {
-        for (int i = rg + kFirstLater; i < L; i += NRG) {
-          const float4 uv = ld4(Ub + size_t(i) * DV + 4 * cg);
-          if constexpr (CF::NEEDS_C) cv = fma4(s_gk[i], uv, cv);
-          ov = fma4(s_gq[i], uv, ov);
-          if (stage_u && i < CF::CH) s_u[i * NCG + cg] = uv;
+        if ((DL == 1 || CF::BONUS) && stage) {
+#pragma unroll
+          for (int x = 0; x < RPL; ++x) {
+            const int pr = x * LPE + c_;
+            float kx = kr_raw[a].at(x);
+            if constexpr (DL != 1) kx *= dl_exp(s_lm[pr] - lr_raw[a].at(x));
+            else kx *= wt;
+            s_kt[pr * KTS + i] = live ? kx : 0.f;
+            if (CF::LEAN && x % 4 == 3) sched_fence();
+          }
+        }
+        if constexpr (CF::NEEDS_C) ak = group_sum<LPE>(ak);   // the delta-rule correction only
+        aq = group_sum<LPE>(aq);
+        if (c_ == 0 && live) {
+          if constexpr (CF::NEEDS_C) s_gk[i] = ak;
+          s_gq[i] = aq;
         }
       }
     }
-    // Rows of one column group live in lanes NCG apart inside a wave, then across waves.
-    static_assert(NCG == 16 || NCG == 32, "column groups fill one or two 16-lane rows");
+    __syncthreads();
+
+    // ---- 5. log replay: each log value row is read by one row group --------------------
+#pragma unroll
+    for (int a = 0; a < UQ; ++a) {
+      if (a * NRG + w * GW < L) {                 // uniform per wave
+        const int i = a * NRG + rg, ic = min(i, L - 1);
+        const float4 u = u_raw[a].get();
+        if constexpr (CF::NEEDS_C) cv = fma4(i < L ? s_gk[ic] : 0.f, u, cv);
+        ov = fma4(i < L ? s_gq[ic] : 0.f, u, ov);
+      }
+    }
+  }
+
+  float4 bv = f4(0.f);
+  // ---- 6. sums over rows, update factors, output, append -----------------------------
+  // Rows of one column group live in lanes NCG apart inside a wave, then across waves.
+  if constexpr (CF::READS_OUT) {
     if constexpr (NCG == 16) {
       if constexpr (CF::NEEDS_C) cv = xor16_sum(cv);
       ov = xor16_sum(ov);
     }
     if constexpr (CF::NEEDS_C) cv = xor32_sum(cv);
     ov = xor32_sum(ov);
-    if constexpr (CF::NW > 1) {
-      const int w = tid / 64, lane = tid % 64;
-      if (lane < NCG) {
-        if constexpr (CF::NEEDS_C) st4(&s_red[w][0][4 * cg], cv);
-        st4(&s_red[w][1][4 * cg], ov);
-      }
-      __syncthreads();
+    if ((tid & 63) < NCG) {
+      if constexpr (CF::NEEDS_C) st4(&s_red[w * 2 * DV + 4 * cg], cv);
+      st4(&s_red[(w * 2 + 1) * DV + 4 * cg], ov);
+    }
+    __syncthreads();
+    float dot = 0.f;
+    if constexpr (CF::HAS_TOKEN) {
+#pragma unroll
+      for (int x = 0; x < WK; ++x) dot += s_dotw[x];
+    }
+    if constexpr (MODE == M_EAGER) {
+      // Every workgroup goes on to its update: each thread sums its own quad (in the same
+      // order), which saves a barrier and a trip through LDS.
       cv = f4(0.f);
       ov = f4(0.f);
 #pragma unroll
-      for (int w2 = 0; w2 < CF::NW; ++w2) {
-        if constexpr (CF::NEEDS_C) cv = cv + *reinterpret_cast<const float4*>(&s_red[w2][0][4 * cg]);
-        ov = ov + *reinterpret_cast<const float4*>(&s_red[w2][1][4 * cg]);
+      for (int x = 0; x < NW; ++x) {
+        if constexpr (CF::NEEDS_C) cv = cv + *reinterpret_cast<const float4*>(&s_red[x * 2 * DV + 4 * cg]);
+        ov = ov + *reinterpret_cast<const float4*>(&s_red[(x * 2 + 1) * DV + 4 * cg]);
       }
-    }
-  }
-
-  // ---- 7. update factors and output ------------------------------------------------
-  float4 bv = f4(0.f);
-  if constexpr (CF::HAS_TOKEN) {
-    const float4 vv = v_raw.get();
-    float dot = 0.f;
+      const float4 v = v4_raw.get();
+      bv = CF::DELTA ? beta * (v - cv) : v;
+      if (rg == 0) st4(p.o + th * DV + 4 * cg, fma4(dot, bv, ov));
+    } else if (w < WV) {
+      // One thread per value column (every thread summing its whole quad would read NRG
+      // times as much LDS as there are partial sums).
+      float c = 0.f, o = 0.f;
 #pragma unroll
-    for (int w2 = 0; w2 < CF::NW; ++w2) dot += s_dotw[w2];
-    if constexpr (CF::DELTA) {
-      bv = beta * (vv - cv);                // b = beta (v - c)
-      ov = fma4(dot, bv, ov);               // + (q.k) b : post-update readout
-    } else {
-      bv = vv;                              // b = v
-      ov = fma4(dot, vv, ov);               // + (q.k) v, or the RWKV6 bonus (r.(u*k)) v
-    }
-  }
-  if constexpr (CF::READS_OUT) {
-    if (rg == 0) st4(p.o + th * DV + 4 * cg, ov);
-  }
-  if constexpr (MODE == M_READOUT) return;
-
-  // ---- 8a. append (Eq. 5): L < C in STEP mode --------------------------------------
-  if constexpr (MODE == M_STEP) {
-    if (L < C) {
-      const size_t ent = sh * size_t(C) + L;
-      TU* Ud = static_cast<TU*>(p.u_log) + ent * DV + 4 * cg;
-      if (rg == 0) {
-        if constexpr (CF::DELTA) st4(reinterpret_cast<float*>(Ud), bv);
-        else cp4(Ud, static_cast<const TIN*>(p.v) + th * DV + 4 * cg);
+      for (int x = 0; x < NW; ++x) {
+        if constexpr (CF::NEEDS_C) c += s_red[x * 2 * DV + tid];
+        o += s_red[(x * 2 + 1) * DV + tid];
       }
-      TIN* Kd = static_cast<TIN*>(p.k_log) + ent * DK;
-      constexpr int KCH = DK * int(sizeof(TIN)) / 16;   // 16-byte chunks of one key row
-      for (int x = tid; x < KCH; x += NT)
-        reinterpret_cast<uint4*>(Kd)[x] = reinterpret_cast<const uint4*>(kin)[x];
-      if constexpr (CF::DECAY) {
-        for (int x = tid; x < DL; x += NT) {
-          Lw[size_t(L) * LS + x] = s_lm[CF::cp_pos(x)];
+      float b = 0.f;
+      if constexpr (CF::HAS_TOKEN) {
+        const float v = to_f32(v_raw);
+        b = CF::DELTA ? beta * (v - c) : v;
+        o = fmaf(dot, b, o);                      // post-update readout, or the RWKV6 bonus
+      }
+      p.o[th * DV + tid] = o;
+      if constexpr (MODE == M_STEP) {
+        if (L < C) {                              // Eq. 5
+          TU* Ud = static_cast<TU*>(p.u_log) + (sh * size_t(C) + L) * DV;
+          if constexpr (CF::DELTA) reinterpret_cast<float*>(Ud)[tid] = b;
+          else Ud[tid] = v_raw;                   // bit-exact copy
         }
       }
-      if (tid == 0) p.len[sh] = L + 1;
+      if constexpr (CF::CAN_MERGE) s_bv[tid] = b;
+    }
+  }
+  if constexpr (MODE == M_READOUT) return;
+  if constexpr (MODE == M_STEP) {
+    if (L < C) {
+      if (w < WK) {
+        static_cast<TIN*>(p.k_log)[(sh * size_t(C) + L) * DK + tid] = k_raw;
+        if constexpr (CF::DECAY) {
+          if (tid < DL) Lb[size_t(L) * LS + tid] = s_lm[CF::pos(tid)];
+        }
+        if (tid == 0) len[sh] = L + 1;
+      }
       return;
     }
   }
 
-  // ---- 8b. materialise (Eq. 6 / Eq. 7 / Eq. 3) ---------------------------------------
+  // ---- 7. materialise (Eq. 6 / Eq. 7 / Eq. 3) ------------------------------------------
   if constexpr (CF::CAN_MERGE) {
-    float4 m[RPT];                                  // the materialised rows, fp32
-#pragma unroll
-    for (int j = 0; j < RPT; ++j) {
-      const int r = rg + NRG * j;
-      m[j] = s_em[r] * t[j].get();
-      if constexpr (CF::HAS_TOKEN) m[j] = fma4(s_kf[CF::cp_pos_group(rg, j)], bv, m[j]);
-    }
-    // The contraction on MFMA.  An fp32 state is stored straight from the
-    // accumulators; a bf16 state is rounded from them.
-    using MM = MfmaMerge<NCG, RPT>;
-    constexpr bool kMfma = DL_MFMA_MERGE && (NCG == 32 || DL_MFMA_MERGE_64COL) &&
-                           CF::MERGES_LOG && (sizeof(TS) == 4 || DL_MFMA_MERGE_BF16_STATE);
-    static_assert(kMfma || !CF::KT_PADDED || !CF::MERGES_LOG,
-                  "the VALU contraction reads K~ rows as float4: unpadded layout only");
-    MM mm;
+    constexpr bool kBvLds = CF::HAS_TOKEN && MODE != M_EAGER;
+    if constexpr (kBvLds) __syncthreads();        // s_bv written, the partial sums read
+    if constexpr (kBvLds) bv = *reinterpret_cast<const float4*>(&s_bv[4 * cg]);
     if constexpr (CF::MERGES_LOG) {
-      // Log values of chunk c >= 1 (chunk 0 was staged by the replay): UPT quads per
-      // thread, loaded before the previous chunk's contraction where DL_U_EARLY.
-      constexpr int UPT = CF::UPT;
-      float4 ur[UPT];
-      // Loaded unconditionally (entries past the live length re-read entry L-1) and
-      // zeroed when staged: a load under a per-lane condition would be waited for at
-      // once.
-      Raw4<TU> ur_raw[UPT];
-      int u_c0 = 0;
-      auto load_u = [&](int c0) {
-        u_c0 = c0;
+      if (L > 0) {                                // uniform
+        if constexpr (CF::REPLAYS) {              // log values from the replay's registers
 #pragma unroll
-        for (int k = 0; k < UPT; ++k) {
-          const int x = tid + k * NT, ii = x / NCG, c4 = x % NCG;
-          ur_raw[k].load(Ub + size_t(min(c0 + ii, L - 1)) * DV + 4 * c4);
-        }
-      };
-      auto widen_u = [&]() {
+          for (int a = 0; a < UQ; ++a) {
+            const int i = a * NRG + rg;
+            if (i < CE) s_u[i * NCG + cg] = i < L ? u_raw[a].get() : f4(0.f);
+          }
+        } else {                                  // flush: keys and values from memory
 #pragma unroll
-        for (int k = 0; k < UPT; ++k) {
-          const int ii = (tid + k * NT) / NCG;
-          ur[k] = (u_c0 + ii < L) ? ur_raw[k].get() : f4(0.f);
-        }
-      };
-      const int first_global = CF::REPLAYS ? CF::CH : 0;   // first chunk whose U is loaded here
-      // A bf16 state leaves no registers for holding the next chunk's values.
-      constexpr bool kUEarly = CF::U_EARLY && sizeof(TS) == 4;
-      if (kUEarly && first_global < L) load_u(first_global);
-      // Decayed keys of the chunks the coefficient passes did not stage: the same run
-      // layout as the passes (entry e_ of the chunk, rows c_ RPL .. c_ RPL + RPL - 1, one
-      // 16-byte key load and the snapshots of the run), loaded one chunk ahead where
-      // kUEarly, and written to LDS chunk slot 0 (free once chunk 0 is contracted).
-      RawRun<TIN, RPL> kg_raw{};
-      RawRun<float, (DL == 1) ? 8 : RPL> lg_raw{};
-      float lg0 = 0.f;
-      auto load_kt = [&](int c0) {
-        const int ig = min(c0 + e_, L - 1);       // lanes past L re-read entry L-1 (unused)
-        kg_raw.load(Kb + size_t(ig) * DK + c_ * RPL);
-        if constexpr (CF::DECAY) {
-          if constexpr (DL == 1) lg0 = Lb[size_t(ig) * LS];
-          else lg_raw.load(Lb + size_t(ig) * DK + c_ * RPL);
-        }
-      };
-      auto store_kt = [&](int c0) {
-        float kv[RPL];
-        kg_raw.get(kv);
-        // Entries past the live length (re-reads of entry L-1, finite) get a factor of
-        // 0 rather than a branch, so that neither load is moved under a per-lane
-        // condition and waited for there.
-        const float live = c0 + e_ < L ? 1.f : 0.f;
-        if constexpr (DL == 1) {
-          const float w = live * (CF::DECAY ? dl_exp(s_lm[0] - lg0) : 1.f);
+          for (int a = 0; a < NP; ++a) {
+            if (ew < EPP) {
+              const int i = a * EPP + e_, ic = min(i, L - 1);
+              RawRun<TIN, RPL> kg;
+              RawRun<float, DL == 1 ? 4 : RPL> lg;
+              kg.load(Kb + size_t(ic) * DK + c_ * RPL);
+              float wt = 1.f;
+              if constexpr (DL != 1) lg.load(Lb + size_t(ic) * DK + c_ * RPL);
+              else if constexpr (CF::DECAY) wt = dl_exp(s_lm[0] - Lb[size_t(ic) * LS]);
 #pragma unroll
-          for (int x = 0; x < RPL; ++x) s_kt[CF::kt_off_run(c_, x) + e_] = w * kv[x];
-        } else {
-          float lv[RPL];
-          lg_raw.get(lv);
-#pragma unroll
-          for (int x = 0; x < RPL; ++x) {
-            const float w = live * dl_exp(s_lm[CF::cp_pos_run(c_, x)] - lv[x]);
-            s_kt[CF::kt_off_run(c_, x) + e_] = w * kv[x];
+              for (int x = 0; x < RPL; ++x) {
+                const int pr = x * LPE + c_;
+                if constexpr (DL != 1) wt = dl_exp(s_lm[pr] - lg.at(x));
+                s_kt[pr * KTS + i] = i < L ? wt * kg.at(x) : 0.f;
+              }
+            }
+          }
+          for (int x = tid; x < CE * NCG; x += NT) {
+            const int i = x / NCG;
+            s_u[x] = i < L ? ld4(Ub + size_t(i) * DV + 4 * (x % NCG)) : f4(0.f);
           }
         }
-      };
-      const int first_kt = CF::REPLAYS ? CF::NSTAGE * CF::CH : 0;   // first chunk staged here
-      // Keys and snapshots one chunk ahead only where they fit beside the contraction's
-      // registers at full occupancy (one log-decay per head, or small heads); a 128-row
-      // per-key head loads them after the barrier (recently read: L2 hits).
-      constexpr bool kKtEarly = kUEarly && CF::NSTAGE == 1 && (DL == 1 || RPT <= 8);
-      if (kKtEarly && first_kt < L) load_kt(first_kt);
-      // One chunk in the short STEP build (the MERGE kernel keeps the general loop: its
-      // registers come out lower that way, 112 against 140 for a 128² per-key head).
-      const int chunks_end = (CF::CAP_ONE_PASS && MODE == M_STEP) ? min(L, 1) : L;
-      int a_off[MM::NMB];                           // LDS offset of this lane's A row, per block
-      const int kq = (tid % 64) / NCG;              // the lane's entry within a K-step
-      if constexpr (kMfma) {
-#pragma unroll
-        for (int mb = 0; mb < MM::NMB; ++mb)
-          a_off[mb] = CF::kt_base(CF::kt_row(MM::row_of(tid / 64, mb, cg, NRG))) + kq;
-        mm.from_rows(m);
+        __syncthreads();
       }
-      for (int i0 = 0; i0 < chunks_end; i0 += CF::CH) {         // uniform trip count
-        const int chunk = i0 / CF::CH;
-        const int n = min(CF::CH, L - i0);
-        const bool kt_staged = CF::REPLAYS && chunk < CF::NSTAGE;
-        const float* const kt = s_kt + (kt_staged ? chunk : 0) * CF::KT_CHUNK;
-        __syncthreads();                            // previous chunk consumed / chunk 0 visible
-        if (!(CF::REPLAYS && chunk == 0)) {
-          if (!kt_staged) {                         // K~_i[r] = e^(l'_r - Lam_i,r) K_i[r]
-            if (!kKtEarly) load_kt(i0);
-            store_kt(i0);
-          }
-          if (!kUEarly) load_u(i0);
-          widen_u();
-#pragma unroll
-          for (int k = 0; k < UPT; ++k) s_u[tid + k * NT] = ur[k];
-          if (kUEarly && i0 + CF::CH < L) {         // the next chunk, in flight meanwhile
-            load_u(i0 + CF::CH);
-            if (kKtEarly && i0 + CF::CH >= first_kt) load_kt(i0 + CF::CH);
-          }
-          __syncthreads();
-        }
-        if constexpr (kMfma) {
-          // The operands of the whole chunk are read from LDS up front (the compiler
-          // spreads the reads over the first MFMAs).  The chunk is zero-padded to CH
-          // entries (both K~ and U); the second half is skipped when the chunk holds at
-          // most CH / 2 entries.
-          constexpr int NKS = CF::CH / MM::KS;
-          float a[NKS][MM::NMB];
-          float4 b[NKS];
-#pragma unroll
-          for (int k = 0; k < NKS; ++k) {
-#pragma unroll
-            for (int mb = 0; mb < MM::NMB; ++mb) a[k][mb] = kt[a_off[mb] + k * MM::KS];
-            b[k] = s_u[(k * MM::KS + kq) * NCG + cg];
-          }
-#pragma unroll
-          for (int k = 0; k < NKS / 2; ++k) mm.step(a[k], b[k]);
-          if (n > CF::CH / 2) {
-#pragma unroll
-            for (int k = NKS / 2; k < NKS; ++k) mm.step(a[k], b[k]);
-          }
-          continue;
-        }
-#pragma unroll 1
-        for (int ii = 0; ii < n; ii += 4) {          // zero-padded to a multiple of 4
-          const float4 u0 = s_u[(ii + 0) * NCG + cg];
-          const float4 u1 = s_u[(ii + 1) * NCG + cg];
-          const float4 u2 = s_u[(ii + 2) * NCG + cg];
-          const float4 u3 = s_u[(ii + 3) * NCG + cg];
-#pragma unroll
-          for (int j = 0; j < RPT; ++j) {
-            const float4 k4 =
-                *reinterpret_cast<const float4*>(&kt[CF::kt_base(CF::kt_row_group(rg, j)) + ii]);
-            m[j] = fma4(k4.x, u0, m[j]);
-            m[j] = fma4(k4.y, u1, m[j]);
-            m[j] = fma4(k4.z, u2, m[j]);
-            m[j] = fma4(k4.w, u3, m[j]);
-          }
-        }
-      }
-      if constexpr (kMfma) mm.drain();
     }
-    // The live length is written before the rows, so that no register is written
-    // behind the state stores.
+    // The live length is written before the rows, so that no register is written behind
+    // the state stores.
     if constexpr (CF::HAS_LOG) {
-      if (tid == 0) p.len[sh] = 0;                 // the cumulative log-decay restarts at 0
+      if (tid == 0) len[sh] = 0;                  // the cumulative log-decay restarts at 0
     }
-    if constexpr (kMfma && sizeof(TS) == 4) {
-      mm.store_rows(srs, toff, kRowBlock);
-    } else if constexpr (kMfma) {
-      mm.to_rows(m);
-      StateQuad<TS>::store_rows(srs, toff, kRowBlock, m);
-    } else {
-      StateQuad<TS>::store_rows(srs, toff, kRowBlock, m);
+    // Row blocks of four: an eager step stores each block as soon as it is formed (GDN
+    // 128x32 heads 95.7 -> 91.8 us against two blocks at a time).  A merge forms two at a
+    // time; all four together read each staged log value from LDS once instead of twice,
+    // but their registers cost every append more (GLA 100x32 heads, bf16 state, one cycle
+    // of M = 16: 411 us with two, 414 with four; 8 layers of 8 staggered GDN slots: 59.6
+    // and 61.7).  The rank-L contraction runs on v_mfma_f32_4x4x1f32
+    // (fp32 products and sums, twice the rate of plain FMAs) with the block's rows as the
+    // accumulator: of its 16 independent 4 x 4 products, block l / 4 is that of lanes
+    // 4 b .. 4 b + 3; lane l holds output column l % 4 of its block and all four rows,
+    // i.e. with rows j = 0 .. 3 of the lane's own row group and component c of its own
+    // column quad as the column, accumulator c is component c of the lane's four quads.
+    // The B operand (U) is the lane's own quad; the A operand (K~) is the lane's row
+    // cg % 4, the same for the NCG / 4 blocks of a row group, so each of those blocks
+    // reads another entry and the instruction broadcasts one block's (cbsz, abid).
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int NRB = RPT / 4, RBG = MODE == M_EAGER ? 1 : NRB < 2 ? NRB : 2, NR = 4 * RBG;
+#pragma unroll
+    for (int g = 0; g < NRB; g += RBG) {
+      float4 m[NR];
+#pragma unroll
+      for (int j = 0; j < NR; ++j) {
+        const int r = rg + NRG * (4 * g + j);
+        m[j] = s_em[r] * t[4 * g + j].get();
+        if constexpr (CF::HAS_TOKEN) m[j] = fma4(s_kf[CF::pos(r)], bv, m[j]);
+      }
+      if constexpr (CF::MERGES_LOG) {
+        f32x4 acc[RBG][4];
+        int a_off[RBG];
+#pragma unroll
+        for (int rb = 0; rb < RBG; ++rb) {
+          a_off[rb] = CF::pos(rg + NRG * (4 * (g + rb) + (cg & 3))) * KTS + (cg >> 2);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float4 r = m[4 * rb + i];
+            acc[rb][0][i] = r.x; acc[rb][1][i] = r.y; acc[rb][2][i] = r.z; acc[rb][3][i] = r.w;
+          }
+        }
+        constexpr int EB = NCG / 4;               // entries per read of the A operand
+        constexpr int CB = EB == 8 ? 3 : 2;       // cbsz: log2 of the blocks per broadcast
+        for (int i0 = 0; i0 < L; i0 += EB) {      // zeros past the live length
+          float a[RBG];
+#pragma unroll
+          for (int rb = 0; rb < RBG; ++rb) a[rb] = s_kt[a_off[rb] + i0];
+#define DL_MERGE_ENTRY(e)                                                                   \
+  {                                                                                         \
+    const float4 b = s_u[(i0 + e) * NCG + cg];                                              \
+    _Pragma("unroll") for (int rb = 0; rb < RBG; ++rb) {                                    \
+      acc[rb][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[rb], b.x, acc[rb][0], CB, e, 0);    \
+      acc[rb][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[rb], b.y, acc[rb][1], CB, e, 0);    \
+      acc[rb][2] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[rb], b.z, acc[rb][2], CB, e, 0);    \
+      acc[rb][3] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[rb], b.w, acc[rb][3], CB, e, 0);    \
+    }                                                                                       \
+  }
+          DL_MERGE_ENTRY(0) DL_MERGE_ENTRY(1) DL_MERGE_ENTRY(2) DL_MERGE_ENTRY(3)
+          if constexpr (EB == 8) {
+            if (CF::LEAN) sched_fence();
+            DL_MERGE_ENTRY(4) DL_MERGE_ENTRY(5) DL_MERGE_ENTRY(6) DL_MERGE_ENTRY(7)
+          }
+          if (CF::LEAN) sched_fence();
+#undef DL_MERGE_ENTRY
+        }
+#pragma unroll
+        for (int rb = 0; rb < RBG; ++rb) {
+          // Wait states between the last MFMA and the first VALU read of its results, on
+          // top of those the compiler inserts.
+          asm volatile("s_nop 7\n\ts_nop 7"
+                       : "+v"(acc[rb][0]), "+v"(acc[rb][1]), "+v"(acc[rb][2]), "+v"(acc[rb][3]));
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            m[4 * rb + i] = make_float4(acc[rb][0][i], acc[rb][1][i], acc[rb][2][i], acc[rb][3][i]);
+        }
+      }
+      if constexpr (sizeof(TS) == 4) {
+        // Every row is gathered into registers of its own and all of them stay allocated
+        // until the last store has issued, with wait states before they are reused:
+        // gathered into one reused set of four registers, each row's registers were
+        // rewritten right behind its store, and on the GPU that store then wrote the next
+        // row's value in lanes 12-15 of each 16-lane row now and then.
+        u32x4 x[NR];
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+          x[j] = u32x4{__float_as_uint(m[j].x), __float_as_uint(m[j].y),
+                       __float_as_uint(m[j].z), __float_as_uint(m[j].w)};
+          asm volatile("" : "+v"(x[j]));
+        }
+#pragma unroll
+        for (int j = 0; j < NR; ++j)
+          __builtin_amdgcn_raw_buffer_store_b128(x[j], srs, toff, (4 * g + j) * kRowBlock,
+                                                 kStateStorePolicy);
+#pragma unroll
+        for (int j = 0; j < NR; ++j) asm volatile("s_nop 0" ::"v"(x[j]));
+      } else {
+#pragma unroll
+        for (int j = 0; j < NR; ++j)
+          StateQuad<TS>::store(srs, toff, (4 * g + j) * kRowBlock, m[j]);
+      }
     }
   }
 }

@@ -5,26 +5,31 @@
 
 namespace dl {
 
-template <int OP, int DK, int DV, int MODE, typename TIN, typename TS, bool LONG>
+template <int OP, int DK, int DV, int MODE, typename TIN, typename TS, int CE>
 hipError_t launch_build(const KParams& p, hipStream_t s) {
-  using CF = Cfg<OP, DK, DV, MODE, LONG>;
   const dim3 grid(unsigned(p.n) * unsigned(p.H));
-  const dim3 block(CF::NT);
-  KParams arg = p;
-  void* args[] = {&arg};
+  const dim3 block(threads_per_head(DK, DV, CE));
+  const int32_t* slots = p.slots;
+  int32_t* len = p.len;
+  void* S = p.S;
+  const void *k = p.k, *q = p.q;
+  int H = p.H, n = p.n, C = p.C;
+  uint32_t h_magic = 0xffffffffu / uint32_t(p.H);
+  KParams rest = p;
+  void* args[] = {&slots, &len, &S, &k, &q, &H, &h_magic, &n, &C, &rest};
   return hipLaunchKernel(
-      reinterpret_cast<const void*>(&deltalog_kernel<OP, DK, DV, MODE, TIN, TS, LONG>), grid,
+      reinterpret_cast<const void*>(&deltalog_kernel<OP, DK, DV, MODE, TIN, TS, CE>), grid,
       block, args, 0, s);
 }
 
-// The STEP and MERGE kernels have a second build for logs longer than one coefficient
-// pass (capacity C > 16), picked from the descriptor's merge interval.
+// The build for the descriptor's log capacity (the eager kernel has no log).
 template <int OP, int DK, int DV, int MODE, typename TIN, typename TS>
 hipError_t launch_one(const KParams& p, hipStream_t s) {
-  constexpr bool kHasLong = MODE == M_STEP || MODE == M_MERGE;
-  if (kHasLong && p.C > Cfg<OP, DK, DV, MODE>::CH)
-    return launch_build<OP, DK, DV, MODE, TIN, TS, kHasLong>(p, s);
-  return launch_build<OP, DK, DV, MODE, TIN, TS, false>(p, s);
+  if constexpr (MODE != M_EAGER) {
+    if (log_build(p.C) == 64) return launch_build<OP, DK, DV, MODE, TIN, TS, 64>(p, s);
+    if (log_build(p.C) == 32) return launch_build<OP, DK, DV, MODE, TIN, TS, 32>(p, s);
+  }
+  return launch_build<OP, DK, DV, MODE, TIN, TS, 16>(p, s);
 }
 
 template <int OP, int DK, int DV, typename TIN, typename TS>
