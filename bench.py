@@ -634,7 +634,7 @@ def main():
                   outs[r].data_ptr(), sl_ptr(k), w.B, sp) for k in range(PER)]
                 for r in range(R)]
     if args.tiled:
-        # value-tiled path: [ReplayPrep] + tiles + Finalize per layer and step; one
+        # value-tiled path: ReplayPrep + tiles, or tiles + Finalize, per layer and step; one
         # scratch buffer serves every layer (the launches are ordered on one stream)
         split = not args.fused_replay
         ws = D.tiled_workspace(desc, w.B) if split else None
@@ -844,7 +844,7 @@ def main():
                        "(dl_append_step: append or merge)" if not args.tiled else
                        f"dl_append_step_tiled, {args.tiled} value tiles, "
                        f"{'fused' if args.fused_replay else 'split'} replay: "
-                       "[replay_prep_kernel] + tile_step_kernel + finalize_kernel per call "
+                       "replay_prep_kernel + tile_step_kernel, or tile_step_kernel + finalize_kernel, per call "
                        "(durations and bytes are per call)"),
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS,

@@ -169,21 +169,23 @@ int dl_readout(const dl_desc* desc, const dl_state* state, const void* q, float*
 /* Value-tiled DeltaLog step (Sec. 3.3, the kernel ownership path): the same operation
  * as dl_append_step (results equal up to floating-point reassociation), with each
  * (slot, head) state split along the value dimension into value_tiles tiles of
- * dk x dv/value_tiles, one workgroup each.  Three launches on the stream:
+ * dk x dv/value_tiles, one workgroup each.  Two launches on the stream (one if C == 0):
  *   [ReplayPrep]  split_replay != 0 and C > 0 only: the key-side replay coefficients
  *                 q^T D(ell - Lam_i) K_i and k^T D(ell - Lam_i) K_i of every live entry,
- *                 once per (row, head), into the caller's workspace (fp32);
+ *                 once per (row, head), into the caller's workspace (fp32), and the
+ *                 commit of L (from which the tiles tell the L they act on);
  *   AppendDecode  per value tile: stream the tile, replay the log on its columns (with
  *                 the prepared coefficients, or recomputing them per tile when
  *                 split_replay == 0), write the output slice, append the tile's U_log
  *                 shard (tile 0 also writes K_log[L] and Lam_log[L]) or merge the tile;
- *   Finalize      per (row, head): commit L exactly once.
+ *   [Finalize]    split_replay == 0 and C > 0 only: commit L exactly once per (row, head).
  * value_tiles: 2 or 4.  Only state_dtype == DL_F32 (else DL_E_DTYPE).
  * workspace: device memory of at least dl_tiled_workspace_bytes(desc, n) bytes, 16-byte
  * aligned, owned by the caller; required when split_replay != 0 and C > 0, ignored
  * otherwise.  Its contents are scratch: overwritten, never read across calls.  Calls
  * that share a workspace must not overlap.  If a later launch fails, DL_E_HIP is
- * returned and the earlier launches of the call may already be enqueued. */
+ * returned and the earlier launch of the call may already be enqueued, so the state
+ * must then be taken as partly stepped. */
 int dl_append_step_tiled(const dl_desc* desc, const dl_state* state, const dl_token* tok,
                          float* o, const int32_t* slots, int32_t n, int32_t value_tiles,
                          int32_t split_replay, void* workspace, size_t workspace_bytes,

@@ -1,18 +1,23 @@
 // Value-tiled DeltaLog decode step (Sec. 3.3, the kernel ownership path): the state of
 // one (slot, head) is split along the value dimension into NV tiles of dk x dv/NV, one
-// workgroup per (token row, head, tile), in three stages:
+// workgroup per (token row, head, tile):
 //
 //   replay_prep_kernel  (split replay only) once per (row, head): the key-side replay
 //                       coefficients g_i(k), g_i(q) of every live entry, into an fp32
-//                       scratch buffer [n, H, 2, C] owned by the caller;
+//                       scratch buffer [n, H, 2, C] owned by the caller, and the commit of
+//                       the live length (append: L + 1; merge: 0);
 //   tile_step_kernel    per value tile: stream the dense-base tile, replay the live log
 //                       on the tile's columns (coefficients from the scratch buffer, or
 //                       recomputed by every tile in the fused variant), write the
 //                       output slice, then either append the tile's U_log[L] shard --
 //                       tile 0 being the designated writer of the shared K_log[L] and
 //                       Lam_log[L] -- or merge the tile's columns of the base;
-//   finalize_kernel     once per (row, head): commit L (append: L + 1; merge: 0) after
-//                       every tile has read it.
+//   finalize_kernel     (fused replay only) commit L after every tile has read it.
+//
+// With split replay the length is committed ahead of the tiles: append maps L to L + 1 in
+// 1 .. C and merge maps C to 0, so every committed length has one L it came from and the
+// tiles read that (GDN 32x32 heads 128x128, M = 8, 4 tiles: the launch it saves is about
+// 4 us of the 23.5 us a step took with it).
 //
 // The arithmetic per element is that of dl_kernel.hpp; the coefficient routine is shared
 // by the prepare kernel and the fused tile kernel, so the split and fused variants give
@@ -35,15 +40,34 @@ struct TileCfg {
   static constexpr int NRG = NT / NCG;             // row groups
   static constexpr int RPT = DK / NRG;             // rows per thread
   static constexpr int NW = NT / 64;               // waves
+  static constexpr int WK = DK / 64;               // waves of the per-row work
   static constexpr int CH = 16;                    // log entries staged per merge chunk
   static constexpr int KTS = CH + 4;               // LDS row stride of a staged K~ chunk
-  static_assert(DV % NV == 0 && DVT % 4 == 0, "value tiles of whole column quads");
+  static constexpr int LPE = 16, EPP = NT / LPE, RPL = DK / LPE;   // coefficient pass
+  static constexpr int UQ = 32 / NRG < 1 ? 1 : 32 / NRG;           // log values loaded ahead
+  static_assert(DV % NV == 0 && DVT % 4 == 0 && DVT <= NT, "value tiles of whole column quads");
   static_assert(NT % 64 == 0 && NT >= DK, "whole waves; one thread per key row in the prologue");
-  static_assert(64 % NCG == 0 && NT == NCG * NRG && DK == NRG * RPT, "thread layout");
+  static_assert(64 % NCG == 0 && NT == NCG * NRG && DK == NRG * RPT && RPT % 4 == 0, "thread layout");
 };
+
+// Sum over the lanes of a wave that share a column group (NCG apart).
+template <int NCG>
+__device__ __forceinline__ float column_sum(float v) {
+  static_assert(NCG == 4 || NCG == 8 || NCG == 16 || NCG == 32, "column groups");
+  if constexpr (NCG <= 4) v += dpp_move<0x124>(v);   // row_ror:4
+  if constexpr (NCG <= 8) v += dpp_move<0x128>(v);   // row_ror:8
+  if constexpr (NCG <= 16) v = xor16_sum(v);
+  return xor32_sum(v);
+}
+template <int NCG>
+__device__ __forceinline__ float4 column_sum(float4 v) {
+  return make_float4(column_sum<NCG>(v.x), column_sum<NCG>(v.y), column_sum<NCG>(v.z),
+                     column_sum<NCG>(v.w));
+}
 
 // Replay coefficients of the live entries for the readout vectors k and q (LDS s_kf,
 // s_qf) at readout log-decay s_lr:  g_i(x) = sum_r e^(s_lr[r] - Lam_i,r) x_r K_i,r.
+// The LDS vectors hold row c * RPL + x at x * 16 + c (lane c's run, element x).
 // Every entry is reduced by 16 lanes of dk/16 rows each, whatever the workgroup size, so
 // every caller produces the same bits.  Results go to gk[i], gq[i] (i < L).
 template <int OP, int DK, int NT, typename TIN, typename Sink>
@@ -56,121 +80,146 @@ __device__ __forceinline__ void replay_coefficients(const TIN* Kb, const float* 
   const int tid = threadIdx.x;
   const int e_ = tid / LPE, c_ = tid % LPE;
   for (int i0 = 0; i0 < L; i0 += EPP) {           // uniform trip count
-    const int i = i0 + e_;
+    const int i = i0 + e_, ic = min(i, L - 1);    // lanes past the log re-read its last entry
+    RawRun<TIN, RPL> kr;
+    RawRun<float, DL == 1 ? 4 : RPL> lr;
+    float l0 = 0.f;
+    kr.load(Kb + size_t(ic) * DK + c_ * RPL);
+    if constexpr (TR::DECAY) {
+      if constexpr (DL == 1) l0 = Lb[size_t(ic) * LS];
+      else lr.load(Lb + size_t(ic) * LS + c_ * RPL);
+    }
     float ak = 0.f, aq = 0.f;
-    if (i < L) {
 #pragma unroll
-      for (int x = 0; x < RPL; ++x) {
-        const int r = c_ * RPL + x;
-        float kr = ld1(Kb + size_t(i) * DK + r);
-        if constexpr (TR::DECAY && DL != 1) kr *= dl_exp(s_lr[r] - Lb[size_t(i) * LS + r]);
-        ak = fmaf(kr, s_kf[r], ak);
-        aq = fmaf(kr, s_qf[r], aq);
-      }
-      if constexpr (TR::DECAY && DL == 1) {
-        const float w = dl_exp(s_lr[0] - Lb[size_t(i) * LS]);
-        ak *= w;
-        aq *= w;
-      }
+    for (int x = 0; x < RPL; ++x) {
+      const int pr = x * LPE + c_;
+      float kx = kr.at(x);
+      if constexpr (TR::DECAY && DL != 1) kx *= dl_exp(s_lr[pr] - lr.at(x));
+      if constexpr (TR::DELTA) ak = fmaf(kx, s_kf[pr], ak);
+      aq = fmaf(kx, s_qf[pr], aq);
     }
-#pragma unroll
-    for (int m = LPE / 2; m >= 1; m >>= 1) {
-      ak += shfl_xor(ak, m);
-      aq += shfl_xor(aq, m);
+    if constexpr (TR::DECAY && DL == 1) {
+      const float w = dl_exp(s_lr[0] - l0);
+      ak *= w;
+      aq *= w;
     }
+    if constexpr (TR::DELTA) ak = group_sum<LPE>(ak);
+    aq = group_sum<LPE>(aq);
     if (c_ == 0 && i < L) sink(i, ak, aq);
   }
 }
 
+// LDS position of key row r in the coefficient pass's vectors.
+template <int DK>
+__device__ __forceinline__ int tile_pos(int r) { return (r % (DK / 16)) * 16 + r / (DK / 16); }
+
 // Cumulative log-decay of a (slot, head) at live length L, element x: the newest
 // snapshot, 0 with an empty log (it is not stored; see the step kernel).
-template <int OP, int DK>
-__device__ __forceinline__ float cumulative_decay(const KParams& p, size_t sh, int L, int x) {
-  using TR = OpTraits<OP>;
-  if constexpr (!TR::DECAY) {
-    return 0.f;
-  } else if constexpr (!TR::PER_KEY) {
-    const int slot = int(sh / size_t(p.H)), h = int(sh % size_t(p.H));
-    return L > 0 ? scalar_ld(lam_log_base<1>(p, slot, h) + size_t(L - 1) * lam_log_stride<1>(p))
-                 : 0.f;
-  } else {
-    const int slot = int(sh / size_t(p.H)), h = int(sh % size_t(p.H));
-    return L > 0 ? lam_log_base<DK>(p, slot, h)[size_t(L - 1) * DK + x] : 0.f;
-  }
+template <int DL>
+__device__ __forceinline__ float cumulative_decay(const float* Lb, size_t LS, int L, int x) {
+  if constexpr (DL == 1) return L > 0 ? scalar_ld(Lb + size_t(L - 1) * LS) : 0.f;
+  else return L > 0 ? Lb[size_t(L - 1) * LS + x] : 0.f;
 }
 
-// Live length of a (slot, head) if the row's slot and the length are valid, else -1.
-__device__ __forceinline__ int tiled_row(const KParams& p, int row, int h, size_t& sh) {
-  const int slot = p.slots ? p.slots[row] : row;
-  if (slot < 0 || slot >= p.B) return -1;
-  sh = size_t(slot) * p.H + h;
-  const int L = p.len[sh];
-  return (L < 0 || L > p.C) ? -1 : L;
+// Token row and head of a linear index (see deltalog_kernel for h_magic).
+__device__ __forceinline__ void split_row(uint32_t lin, int H, uint32_t h_magic, int& row, int& h) {
+  row = int(__umulhi(lin, h_magic));
+  h = int(lin) - row * H;
+  if (h >= H) {
+    h -= H;
+    ++row;
+  }
 }
 
 // ------------------------------------------------------------------ ReplayPrep
 template <int OP, int DK, typename TIN>
-__global__ __launch_bounds__(256) void replay_prep_kernel(KParams p, float* coef) {
+__global__ __launch_bounds__(256) void replay_prep_kernel(const int32_t* slots, int32_t* len,
+                                                          const void* k_, const void* q_,
+                                                          float* coef, int H, uint32_t h_magic,
+                                                          int C, KParams p) {
   using TR = OpTraits<OP>;
   constexpr int DL = TR::PER_KEY ? DK : 1;
   __shared__ float s_kf[DK], s_qf[DK], s_lr[DL];
   const int tid = threadIdx.x;
-  const int row = int(blockIdx.x) / p.H, h = int(blockIdx.x) - row * p.H;
-  size_t sh = 0;
-  const int L = tiled_row(p, row, h, sh);          // uniform per workgroup
-  if (L <= 0) return;                              // nothing live (or invalid: reported by the tiles)
-  const size_t th = size_t(row) * p.H + h;
-  if (tid < DK) {
-    s_kf[tid] = to_f32(static_cast<const TIN*>(p.k)[th * DK + tid]);
-    s_qf[tid] = to_f32(static_cast<const TIN*>(p.q)[th * DK + tid]);
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int row, h;
+  split_row(blockIdx.x, H, h_magic, row, h);
+  int slot = row;
+  if (slots) {
+    slot = slots[row];
+    if (slot < 0 || slot >= p.B) return;           // reported by the tiles
   }
-  if (tid < DL) {
-    float lr = 0.f;
-    if constexpr (TR::DECAY) {
-      const float ell = cumulative_decay<OP, DK>(p, sh, L, tid);
-      lr = TR::BONUS ? ell : ell + p.lam[th * DL + tid];   // readout decay, as in the step
+  const size_t sh = size_t(slot) * H + h, th = size_t(row) * H + h;
+  const int L_raw = len[sh];
+  const int rl = min(tid, DK - 1);
+  const TIN k_raw = (static_cast<const TIN*>(k_) + th * DK)[rl];
+  const TIN q_raw = (static_cast<const TIN*>(q_) + th * DK)[rl];
+  float lam = 0.f;
+  if constexpr (TR::DECAY && !TR::BONUS) {
+    if constexpr (DL == 1) lam = scalar_ld(p.lam + th);
+    else lam = p.lam[th * DL + rl];
+  }
+  const float* Lb = nullptr;
+  const size_t LS = DL == 1 ? size_t(H) : size_t(DL);
+  if constexpr (TR::DECAY)
+    Lb = p.lam_log + (DL == 1 ? size_t(slot) * size_t(C) * H + h : sh * size_t(C) * DL);
+  const int L = __builtin_amdgcn_readfirstlane(L_raw);
+  if (L < 0 || L > C) return;                      // reported by the tiles
+  if (L > 0) {                                     // uniform per workgroup
+    if (w < DK / 64) {
+      const int pr = tile_pos<DK>(tid);
+      s_kf[pr] = to_f32(k_raw);
+      s_qf[pr] = to_f32(q_raw);
+      float lr = 0.f;
+      // readout decay, as in the step
+      if constexpr (TR::DECAY) lr = cumulative_decay<DL>(Lb, LS, L, DL == 1 ? 0 : tid) + lam;
+      if (tid < DL) s_lr[pr] = lr;
     }
-    s_lr[tid] = lr;
+    __syncthreads();                               // (also: every wave has read the length)
+    float* out = coef + th * 2 * size_t(C);
+    replay_coefficients<OP, DK, 256>(static_cast<const TIN*>(p.k_log) + sh * size_t(C) * DK, Lb,
+                                     LS, L, s_kf, s_qf, s_lr, [&](int i, float gk, float gq) {
+                                       if constexpr (TR::DELTA) out[i] = gk;
+                                       out[C + i] = gq;
+                                     });
   }
-  __syncthreads();
-  const int C = p.C;
-  float* out = coef + th * 2 * size_t(C);
-  const int slot = int(sh / size_t(p.H));
-  replay_coefficients<OP, DK, 256>(static_cast<const TIN*>(p.k_log) + sh * size_t(C) * DK,
-                                   TR::DECAY ? lam_log_base<DL>(p, slot, h) : nullptr,
-                                   lam_log_stride<DL>(p), L,
-                                   s_kf, s_qf, s_lr, [&](int i, float gk, float gq) {
-                                     out[i] = gk;
-                                     out[C + i] = gq;
-                                   });
+  if (L == 0) __syncthreads();                     // every wave has read the length
+  if (tid == 0) len[sh] = L < C ? L + 1 : 0;
 }
 
 // ------------------------------------------------------------------ tile step
 template <int OP, int DK, int DV, int NV, bool SPLIT, typename TIN>
 __global__ __launch_bounds__(tile_threads(DK, DV, NV))
-void tile_step_kernel(KParams p, const float* __restrict__ coef) {
+void tile_step_kernel(const int32_t* slots, const int32_t* len, void* S_, const void* k_,
+                      const void* q_, int H, uint32_t h_magic, int n, int C, KParams p,
+                      const float* __restrict__ coef) {
   using TC = TileCfg<DK, DV, NV>;
   using TR = OpTraits<OP>;
   using TU = typename UType<OP, TIN>::type;
   constexpr int NT = TC::NT, NCG = TC::NCG, NRG = TC::NRG, RPT = TC::RPT, DVT = TC::DVT;
-  constexpr int CH = TC::CH, KTS = TC::KTS;
+  constexpr int CH = TC::CH, KTS = TC::KTS, WK = TC::WK, LPE = TC::LPE, RPL = TC::RPL;
+  constexpr int EPP = TC::EPP, UQ = TC::UQ, GW = 64 / NCG;
   constexpr int DL = TR::PER_KEY ? DK : 1;
   constexpr bool NEEDS_C = TR::DELTA;
 
-  __shared__ float s_kf[DK], s_qf[DK], s_xk[DK], s_xq[DK], s_em[DK];
-  __shared__ float s_lr[DL], s_lm[DL];
-  __shared__ float s_gk[DL_MAX_MERGE_INTERVAL], s_gq[DL_MAX_MERGE_INTERVAL];
-  __shared__ __align__(16) float s_red[TC::NW][2][DVT];
-  __shared__ float s_dotw[TC::NW];
+  __shared__ float s_kf[DK], s_qf[DK];             // coefficient-pass order
+  __shared__ float2 s_x[DK];
+  __shared__ float s_em[DK];
+  __shared__ float s_lr[DL], s_lm[DL];             // coefficient-pass order
+  constexpr int NG = SPLIT ? 1 : DL_MAX_MERGE_INTERVAL;
+  __shared__ float s_gk[NG], s_gq[NG];             // replay coefficients (fused)
+  __shared__ __align__(16) float s_red[TC::NW * 2 * DVT];
+  __shared__ float s_dotw[WK];
+  __shared__ __align__(16) float s_bv[DVT];
   __shared__ __align__(16) float s_kt[DK * KTS];   // K~ chunk [DK][KTS] (merge)
   __shared__ float4 s_u[CH * NCG];                 // U chunk  [CH][NCG] (merge)
 
   const int tid = threadIdx.x;
-  const int H = p.H;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   // Chunks of consecutive (row, head, tile) triples are dealt to the XCDs in turn (as in
   // the untiled kernel); a head's tiles sit in one chunk and share one L2.
   uint32_t lin = blockIdx.x;
-  const uint32_t nblk = gridDim.x;
+  const uint32_t nblk = uint32_t(n) * uint32_t(H) * NV;
   if constexpr (kXcdChunk > 0) {
     const uint32_t full = nblk - nblk % (kXcds * kXcdChunk);
     if (lin < full) {
@@ -179,260 +228,336 @@ void tile_step_kernel(KParams p, const float* __restrict__ coef) {
     }
   }
   const int j = int(lin % NV);                     // value tile
-  const int rh = int(lin / NV);
-  const int row = rh / H, h = rh - row * H;
-  const int slot = p.slots ? p.slots[row] : row;
-  if (slot < 0 || slot >= p.B) {
-    if (tid == 0 && p.err) atomicOr(p.err, 1);
-    return;
+  int row, h;
+  split_row(lin / NV, H, h_magic, row, h);
+  int slot = row;
+  if (slots) {
+    slot = slots[row];
+    if (slot < 0 || slot >= p.B) {
+      if (tid == 0 && p.err) atomicOr(p.err, 1);
+      return;
+    }
   }
   const size_t sh = size_t(slot) * H + h;
   const size_t th = size_t(row) * H + h;
-  const int C = p.C;
-  const int L = p.len[sh];
-  if (L < 0 || L > C) {
-    if (tid == 0 && p.err) atomicOr(p.err, 2);
-    return;
-  }
 
+  // ---- loads: length, token rows, the tile slice, then the log (as in the step kernel) --
+  const int L_raw = len[sh];
+  const int rl = min(tid, DK - 1), cl = min(tid, DVT - 1);
+  const TIN k_raw = (static_cast<const TIN*>(k_) + th * DK)[rl];
+  const TIN q_raw = (static_cast<const TIN*>(q_) + th * DK)[rl];
+  float lam = 0.f, uf = 0.f, beta = 0.f;
+  if constexpr (TR::DECAY && DL != 1) lam = p.lam[th * DL + rl];
+  sched_fence();
   const int cg = tid % NCG, rg = tid / NCG;
   const int c0 = j * DVT + 4 * cg;                 // this thread's first value column
-  const TIN* kin = static_cast<const TIN*>(p.k) + th * DK;
-  const TIN* qin = static_cast<const TIN*>(p.q) + th * DK;
-
-  // ---- tile slice (rows rg + NRG * i, columns c0 .. c0 + 3) --------------------------
-  float* const Sh = static_cast<float*>(p.S) + sh * size_t(DK) * DV;
+  // rows rg + NRG * i, columns c0 .. c0 + 3
+  float* const Sh = static_cast<float*>(S_) + sh * size_t(DK) * DV;
   const auto srs = state_rsrc(Sh, DK * DV * sizeof(float));
   const uint32_t toff = uint32_t(rg * DV + c0) * sizeof(float);
   constexpr uint32_t kRowBlock = NRG * DV * sizeof(float);
   StateQuad<float> t[RPT];
 #pragma unroll
   for (int i = 0; i < RPT; ++i) t[i].load(srs, toff, i * kRowBlock);
+  if constexpr (TR::DECAY && DL == 1) lam = scalar_ld(p.lam + th);
+  if constexpr (TR::BONUS) uf = p.u[size_t(h) * DK + rl];
+  const TIN v_raw = (static_cast<const TIN*>(p.v) + th * DV + j * DVT)[cl];
+  if constexpr (TR::DELTA) beta = scalar_ld(p.beta + th);
+  const TIN* Kb = static_cast<const TIN*>(p.k_log) + sh * size_t(C) * DK;
+  const TU* Ub = static_cast<const TU*>(p.u_log) + sh * size_t(C) * DV;
+  float* Lb = nullptr;
+  const size_t LS = DL == 1 ? size_t(H) : size_t(DL);
+  if constexpr (TR::DECAY)
+    Lb = p.lam_log + (DL == 1 ? size_t(slot) * size_t(C) * H + h : sh * size_t(C) * DL);
+  asm volatile("" ::"s"(Kb), "s"(Ub), "s"(Lb), "s"(coef));
+  sched_fence();
+
+  int L = __builtin_amdgcn_readfirstlane(L_raw);
+  if (L < 0 || L > C) {
+    if (tid == 0 && p.err) atomicOr(p.err, 2);
+    return;
+  }
+  // Split replay: the length is already committed (C == 0 has no prepare launch and
+  // nothing to commit).
+  if constexpr (SPLIT) L = L == 0 ? C : L - 1;
+  // The log values of this row group and, with split replay, their prepared coefficients.
+  Raw4<TU> u_raw[UQ];
+  float gk[UQ] = {}, gq[UQ] = {};
+  const float* const cp = SPLIT ? coef + th * 2 * size_t(C) : nullptr;
+#pragma unroll
+  for (int a = 0; a < UQ; ++a) {
+    if (a * NRG + w * GW < L) {                    // uniform per wave
+      const int ic = min(a * NRG + rg, L - 1);
+      u_raw[a].load(Ub + size_t(ic) * DV + c0);
+      if constexpr (SPLIT) {
+        if constexpr (NEEDS_C) gk[a] = cp[ic];
+        gq[a] = cp[C + ic];
+      }
+    }
+  }
 
   // ---- prologue: per-row decay factors, token vectors, the token dot product --------
-  float kf = 0.f, qf = 0.f, uf = 0.f;
-  if (tid < DK) {
-    kf = to_f32(kin[tid]);
-    qf = to_f32(qin[tid]);
-    if constexpr (TR::BONUS) uf = p.u[size_t(h) * DK + tid];
-    float ell = 0.f, lam = 0.f;
-    if constexpr (TR::DECAY) {
-      ell = cumulative_decay<OP, DK>(p, sh, L, DL == 1 ? 0 : tid);
-      lam = p.lam[th * DL + (DL == 1 ? 0 : tid)];
-    }
+  if (w < WK) {
+    float ell = 0.f;
+    if constexpr (TR::DECAY) ell = cumulative_decay<DL>(Lb, LS, L, DL == 1 ? 0 : tid);
+    const float kf = to_f32(k_raw), qf = to_f32(q_raw);
     const float lm = ell + lam;
     const float lr = TR::BONUS ? ell : lm;
     const float er = dl_exp(lr);
-    s_kf[tid] = kf;
-    s_qf[tid] = qf;
-    s_xk[tid] = er * kf;
-    s_xq[tid] = er * qf;
+    const int pr = tile_pos<DK>(tid);
+    s_kf[pr] = kf;
+    s_qf[pr] = qf;
+    s_x[tid] = make_float2(er * kf, er * qf);
     s_em[tid] = dl_exp(lm);
     if (tid < DL) {
-      s_lr[tid] = lr;
-      s_lm[tid] = lm;
+      s_lr[pr] = lr;
+      s_lm[pr] = lm;
     }
-  }
-  {
-    float d = tid < DK ? (TR::BONUS ? qf * uf * kf : qf * kf) : 0.f;
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) d += shfl_xor(d, m);
-    if ((tid & 63) == 0) s_dotw[tid >> 6] = d;
-  }
-  const float4 vv = ld4(static_cast<const TIN*>(p.v) + th * DV + c0);
-  float beta = 0.f;
-  if constexpr (TR::DELTA) beta = p.beta[th];
-  const TIN* Kb = static_cast<const TIN*>(p.k_log) + sh * size_t(C) * DK;
-  float* const Lw = TR::DECAY ? lam_log_base<DL>(p, slot, h) : nullptr;
-  const float* Lb = Lw;
-  const size_t LS = lam_log_stride<DL>(p);
-  const TU* Ub = static_cast<const TU*>(p.u_log) + sh * size_t(C) * DV;
-  __syncthreads();
-
-  // ---- replay coefficients ------------------------------------------------------------
-  if constexpr (SPLIT) {
-    const float* cp = coef + th * 2 * size_t(C);
-    for (int i = tid; i < L; i += NT) {
-      s_gk[i] = cp[i];
-      s_gq[i] = cp[C + i];
-    }
-  } else {
-    replay_coefficients<OP, DK, NT>(Kb, Lb, LS, L, s_kf, s_qf, s_lr, [&](int i, float gk, float gq) {
-      s_gk[i] = gk;
-      s_gq[i] = gq;
-    });
+    float d = TR::BONUS ? qf * uf * kf : qf * kf;
+    d = xor32_sum(xor16_sum(group_sum<16>(d)));
+    if ((tid & 63) == 0) s_dotw[w] = d;
   }
   __syncthreads();
 
-  // ---- base readouts of the tile's columns plus log replay, reduced over rows -------
+  // ---- base readout of the tile's columns, replay coefficients, log replay -----------
   float4 cv = f4(0.f), ov = f4(0.f);
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
-    const int r = rg + NRG * i;
+    const float2 x = s_x[rg + NRG * i];
     const float4 sj = t[i].get();
-    if constexpr (NEEDS_C) cv = fma4(s_xk[r], sj, cv);
-    ov = fma4(s_xq[r], sj, ov);
+    if constexpr (NEEDS_C) cv = fma4(x.x, sj, cv);
+    ov = fma4(x.y, sj, ov);
   }
-  for (int i = rg; i < L; i += NRG) {
-    const float4 uv = ld4(Ub + size_t(i) * DV + c0);
-    if constexpr (NEEDS_C) cv = fma4(s_gk[i], uv, cv);
-    ov = fma4(s_gq[i], uv, ov);
-  }
-#pragma unroll
-  for (int m = NCG; m < 64; m <<= 1) {
-    if constexpr (NEEDS_C) {
-      cv.x += shfl_xor(cv.x, m); cv.y += shfl_xor(cv.y, m);
-      cv.z += shfl_xor(cv.z, m); cv.w += shfl_xor(cv.w, m);
-    }
-    ov.x += shfl_xor(ov.x, m); ov.y += shfl_xor(ov.y, m);
-    ov.z += shfl_xor(ov.z, m); ov.w += shfl_xor(ov.w, m);
-  }
-  if constexpr (TC::NW > 1) {
-    const int w = tid / 64, lane = tid % 64;
-    if (lane < NCG) {
-      if constexpr (NEEDS_C) st4(&s_red[w][0][4 * cg], cv);
-      st4(&s_red[w][1][4 * cg], ov);
-    }
+  if constexpr (!SPLIT) {
+    replay_coefficients<OP, DK, NT>(Kb, Lb, LS, L, s_kf, s_qf, s_lr, [&](int i, float gk, float gq) {
+      if constexpr (NEEDS_C) s_gk[i] = gk;
+      s_gq[i] = gq;
+    });
     __syncthreads();
-    cv = f4(0.f);
-    ov = f4(0.f);
-#pragma unroll
-    for (int w2 = 0; w2 < TC::NW; ++w2) {
-      if constexpr (NEEDS_C) cv = cv + *reinterpret_cast<const float4*>(&s_red[w2][0][4 * cg]);
-      ov = ov + *reinterpret_cast<const float4*>(&s_red[w2][1][4 * cg]);
-    }
   }
-
-  // ---- update factors and the output slice --------------------------------------------
-  float dot = 0.f;
 #pragma unroll
-  for (int w2 = 0; w2 < TC::NW; ++w2) dot += s_dotw[w2];
-  const float4 bv = TR::DELTA ? beta * (vv - cv) : vv;
-  ov = fma4(dot, bv, ov);
-  if (rg == 0) st4(p.o + th * DV + c0, ov);
-
-  // ---- append (Eq. 5): the tile's U_log shard; tile 0 writes the shared entries ------
-  if (L < C) {
-    const size_t ent = sh * size_t(C) + L;
-    if (rg == 0) {
-      TU* Ud = static_cast<TU*>(p.u_log) + ent * DV + c0;
-      if constexpr (TR::DELTA) st4(reinterpret_cast<float*>(Ud), bv);
-      else cp4(Ud, static_cast<const TIN*>(p.v) + th * DV + c0);
-    }
-    if (j == 0) {
-      TIN* Kd = static_cast<TIN*>(p.k_log) + ent * DK;
-      constexpr int KCH = DK * int(sizeof(TIN)) / 16;
-      for (int x = tid; x < KCH; x += NT)
-        reinterpret_cast<uint4*>(Kd)[x] = reinterpret_cast<const uint4*>(kin)[x];
-      if constexpr (TR::DECAY)
-        for (int x = tid; x < DL; x += NT) Lw[size_t(L) * LS + x] = s_lm[x];
-    }
-    return;                                        // L: finalize_kernel
-  }
-
-  // ---- merge (Eq. 6) of the tile's columns -------------------------------------------
-  float4 m[RPT];
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    const int r = rg + NRG * i;
-    m[i] = fma4(s_kf[r], bv, s_em[r] * t[i].get());
-  }
-  for (int i0 = 0; i0 < L; i0 += CH) {              // uniform trip count
-    const int n = min(CH, L - i0);
-    __syncthreads();                                // the previous chunk is consumed
-    for (int x = tid; x < DK * CH; x += NT) {
-      const int r = x % DK, ii = x / DK;
-      float val = 0.f;
-      if (ii < n) {
-        const int i = i0 + ii;
-        val = ld1(Kb + size_t(i) * DK + r);
-        if constexpr (TR::DECAY)
-          val *= dl_exp(s_lm[DL == 1 ? 0 : r] - Lb[size_t(i) * LS + (DL == 1 ? 0 : r)]);
+  for (int a = 0; a < UQ; ++a) {
+    if (a * NRG + w * GW < L) {                    // uniform per wave
+      const int i = a * NRG + rg, ic = min(i, L - 1);
+      const float4 u = u_raw[a].get();
+      if constexpr (!SPLIT) {
+        if constexpr (NEEDS_C) gk[a] = s_gk[ic];
+        gq[a] = s_gq[ic];
       }
-      s_kt[r * KTS + ii] = val;                     // K~_i[r] = e^(l'_r - Lam_i,r) K_i[r]
+      if constexpr (NEEDS_C) cv = fma4(i < L ? gk[a] : 0.f, u, cv);
+      ov = fma4(i < L ? gq[a] : 0.f, u, ov);
+    }
+  }
+  for (int i = UQ * NRG + rg; i < L; i += NRG) {   // entries past those loaded ahead
+    const float4 u = ld4(Ub + size_t(i) * DV + c0);
+    if constexpr (NEEDS_C) cv = fma4(SPLIT ? cp[i] : s_gk[i], u, cv);
+    ov = fma4(SPLIT ? cp[C + i] : s_gq[i], u, ov);
+  }
+  if constexpr (NEEDS_C) cv = column_sum<NCG>(cv);
+  ov = column_sum<NCG>(ov);
+  if ((tid & 63) < NCG) {
+    if constexpr (NEEDS_C) st4(&s_red[w * 2 * DVT + 4 * cg], cv);
+    st4(&s_red[(w * 2 + 1) * DVT + 4 * cg], ov);
+  }
+  __syncthreads();
+
+  // ---- update factors, the output slice and the append (Eq. 5), one thread per column ---
+  if (tid < DVT) {
+    float c = 0.f, o = 0.f, dot = 0.f;
+#pragma unroll
+    for (int x = 0; x < TC::NW; ++x) {
+      if constexpr (NEEDS_C) c += s_red[x * 2 * DVT + tid];
+      o += s_red[(x * 2 + 1) * DVT + tid];
+    }
+#pragma unroll
+    for (int x = 0; x < WK; ++x) dot += s_dotw[x];
+    const float v = to_f32(v_raw);
+    const float b = TR::DELTA ? beta * (v - c) : v;
+    p.o[th * DV + j * DVT + tid] = fmaf(dot, b, o);
+    if (L < C) {
+      TU* Ud = static_cast<TU*>(p.u_log) + (sh * size_t(C) + L) * DV + j * DVT;
+      if constexpr (TR::DELTA) reinterpret_cast<float*>(Ud)[tid] = b;
+      else Ud[tid] = v_raw;
+    }
+    s_bv[tid] = b;
+  }
+  if (L < C) {                                     // tile 0 writes the shared entries
+    if (j == 0 && w < WK) {
+      static_cast<TIN*>(p.k_log)[(sh * size_t(C) + L) * DK + tid] = k_raw;
+      if constexpr (TR::DECAY) {
+        if (tid < DL) Lb[size_t(L) * LS + tid] = s_lm[tile_pos<DK>(tid)];
+      }
+    }
+    return;
+  }
+
+  // ---- merge (Eq. 6) of the tile's columns, on MFMA as in the step kernel --------------
+  __syncthreads();
+  const float4 bv = *reinterpret_cast<const float4*>(&s_bv[4 * cg]);
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  constexpr int NRB = RPT / 4;
+  f32x4 acc[NRB][4];
+  int a_off[NRB];
+  constexpr int EB = NCG / 4;                      // entries per read of the A operand
+  constexpr int CB = EB == 4 ? 2 : EB == 2 ? 1 : 0;
+  static_assert(EB == 1 || EB == 2 || EB == 4, "blocks of a row group");
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb) {
+    a_off[rb] = tile_pos<DK>(rg + NRG * (4 * rb + (cg & 3))) * KTS + (cg >> 2);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = rg + NRG * (4 * rb + i);
+      const float4 m = fma4(s_kf[tile_pos<DK>(r)], bv, s_em[r] * t[4 * rb + i].get());
+      acc[rb][0][i] = m.x; acc[rb][1][i] = m.y; acc[rb][2][i] = m.z; acc[rb][3][i] = m.w;
+    }
+  }
+  const int e_ = tid / LPE, c_ = tid % LPE;
+  for (int i0 = 0; i0 < L; i0 += CH) {              // uniform trip count
+    const int nn = min(CH, L - i0);
+    if (i0 > 0) __syncthreads();                    // the previous chunk is consumed
+#pragma unroll
+    for (int e0 = 0; e0 < CH; e0 += EPP) {          // K~_i[r] = e^(l'_r - Lam_i,r) K_i[r]
+      const int e = e0 + e_, i = i0 + e, ic = min(i, L - 1);
+      if (e < CH) {
+        RawRun<TIN, RPL> kg;
+        RawRun<float, DL == 1 ? 4 : RPL> lg;
+        float wt = 1.f;
+        kg.load(Kb + size_t(ic) * DK + c_ * RPL);
+        if constexpr (DL != 1) lg.load(Lb + size_t(ic) * LS + c_ * RPL);
+        else if constexpr (TR::DECAY) wt = dl_exp(s_lm[0] - Lb[size_t(ic) * LS]);
+#pragma unroll
+        for (int x = 0; x < RPL; ++x) {
+          const int pr = x * LPE + c_;
+          if constexpr (DL != 1) wt = dl_exp(s_lm[pr] - lg.at(x));
+          s_kt[pr * KTS + e] = i < L ? wt * kg.at(x) : 0.f;
+        }
+      }
     }
     for (int x = tid; x < CH * NCG; x += NT) {
       const int ii = x / NCG, c4 = x % NCG;
-      s_u[x] = ii < n ? ld4(Ub + size_t(i0 + ii) * DV + j * DVT + 4 * c4) : f4(0.f);
+      s_u[x] = ii < nn ? ld4(Ub + size_t(i0 + ii) * DV + j * DVT + 4 * c4) : f4(0.f);
     }
     __syncthreads();
-    for (int ii = 0; ii < n; ii += 4) {             // zero-padded to a multiple of 4
-      const float4 u0 = s_u[(ii + 0) * NCG + cg];
-      const float4 u1 = s_u[(ii + 1) * NCG + cg];
-      const float4 u2 = s_u[(ii + 2) * NCG + cg];
-      const float4 u3 = s_u[(ii + 3) * NCG + cg];
+    for (int ii = 0; ii < nn; ii += 4) {            // zero-padded to a multiple of 4
 #pragma unroll
-      for (int i = 0; i < RPT; ++i) {
-        const int r = rg + NRG * i;
-        const float4 kt = *reinterpret_cast<const float4*>(&s_kt[r * KTS + ii]);
-        m[i] = fma4(kt.x, u0, m[i]);
-        m[i] = fma4(kt.y, u1, m[i]);
-        m[i] = fma4(kt.z, u2, m[i]);
-        m[i] = fma4(kt.w, u3, m[i]);
+      for (int e4 = 0; e4 < 4; e4 += EB) {
+        float a[NRB];
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) a[rb] = s_kt[a_off[rb] + ii + e4];
+#define DL_MERGE_ENTRY(e)                                                                   \
+  if constexpr (e < EB) {                                                                   \
+    const float4 b = s_u[(ii + e4 + e) * NCG + cg];                                         \
+    _Pragma("unroll") for (int rb = 0; rb < NRB; ++rb) {                                    \
+      acc[rb][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[rb], b.x, acc[rb][0], CB, e % EB, 0); \
+      acc[rb][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[rb], b.y, acc[rb][1], CB, e % EB, 0); \
+      acc[rb][2] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[rb], b.z, acc[rb][2], CB, e % EB, 0); \
+      acc[rb][3] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[rb], b.w, acc[rb][3], CB, e % EB, 0); \
+    }                                                                                       \
+  }
+        DL_MERGE_ENTRY(0) DL_MERGE_ENTRY(1) DL_MERGE_ENTRY(2) DL_MERGE_ENTRY(3)
+#undef DL_MERGE_ENTRY
       }
     }
   }
+  // Rows gathered into registers of their own and held until the last store has issued
+  // (see the step kernel).
+  u32x4 x[RPT];
 #pragma unroll
-  for (int i = 0; i < RPT; ++i) StateQuad<float>::store(srs, toff, i * kRowBlock, m[i]);
+  for (int rb = 0; rb < NRB; ++rb) {
+    asm volatile("s_nop 7\n\ts_nop 7"
+                 : "+v"(acc[rb][0]), "+v"(acc[rb][1]), "+v"(acc[rb][2]), "+v"(acc[rb][3]));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[4 * rb + i] = u32x4{__float_as_uint(acc[rb][0][i]), __float_as_uint(acc[rb][1][i]),
+                            __float_as_uint(acc[rb][2][i]), __float_as_uint(acc[rb][3][i])};
+      asm volatile("" : "+v"(x[4 * rb + i]));
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < RPT; ++i)
+    __builtin_amdgcn_raw_buffer_store_b128(x[i], srs, toff, i * kRowBlock, kStateStorePolicy);
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) asm volatile("" ::"v"(x[i]));
 }
 
 // ------------------------------------------------------------------ Finalize
-// One wave per (row, head): append -> L + 1; merge -> L = 0.  The cumulative log-decay
+// One thread per (row, head): append -> L + 1; merge -> L = 0.  The cumulative log-decay
 // follows from Lam_log[L] (written by tile 0) and L, so L is all there is to commit.
-template <int OP, int DK>
-__global__ __launch_bounds__(64) void finalize_kernel(KParams p) {
-  const int tid = threadIdx.x;
-  const int row = int(blockIdx.x) / p.H, h = int(blockIdx.x) - row * p.H;
-  size_t sh = 0;
-  const int L = tiled_row(p, row, h, sh);           // every lane reads L before lane 0 writes it
-  if (L < 0) return;                                // invalid: reported by the tiles
-  if (L < p.C) {
-    if (tid == 0) p.len[sh] = L + 1;
-  } else {
-    if (tid == 0) p.len[sh] = 0;
-  }
+template <int OP>
+__global__ __launch_bounds__(256) void finalize_kernel(const int32_t* slots, int32_t* len,
+                                                       int n, int H, uint32_t h_magic,
+                                                       int B, int C) {
+  const uint32_t lin = blockIdx.x * 256u + threadIdx.x;
+  if (lin >= uint32_t(n) * uint32_t(H)) return;
+  int row, h;
+  split_row(lin, H, h_magic, row, h);
+  const int slot = slots ? slots[row] : row;
+  if (slot < 0 || slot >= B) return;                // invalid: reported by the tiles
+  const size_t sh = size_t(slot) * H + h;
+  const int L = len[sh];
+  if (L < 0 || L > C) return;                       // invalid: reported by the tiles
+  len[sh] = L < C ? L + 1 : 0;
 }
 
 // ------------------------------------------------------------------ dispatch
 template <int OP, int DK, int DV, int NV, bool SPLIT, typename TIN>
 hipError_t launch_tiled_one(const KParams& p, const float* coef, hipStream_t s) {
   using TC = TileCfg<DK, DV, NV>;
-  KParams arg = p;
+  const int32_t* slots = p.slots;
+  const int32_t* len = p.len;
+  void* S = p.S;
+  const void *k = p.k, *q = p.q;
+  int H = p.H, n = p.n, C = p.C;
+  uint32_t h_magic = 0xffffffffu / uint32_t(p.H);
+  KParams rest = p;
   const float* carg = coef;
-  void* args[] = {&arg, &carg};
+  void* args[] = {&slots, &len, &S, &k, &q, &H, &h_magic, &n, &C, &rest, &carg};
   return hipLaunchKernel(reinterpret_cast<const void*>(&tile_step_kernel<OP, DK, DV, NV, SPLIT, TIN>),
                          dim3(unsigned(p.n) * unsigned(p.H) * NV), dim3(TC::NT), args, 0, s);
 }
 
 template <int OP, int DK, typename TIN>
 hipError_t launch_prep(const KParams& p, float* coef, hipStream_t s) {
-  KParams arg = p;
+  const int32_t* slots = p.slots;
+  int32_t* len = p.len;
+  const void *k = p.k, *q = p.q;
   float* carg = coef;
-  void* args[] = {&arg, &carg};
+  int H = p.H, C = p.C;
+  uint32_t h_magic = 0xffffffffu / uint32_t(p.H);
+  KParams rest = p;
+  void* args[] = {&slots, &len, &k, &q, &carg, &H, &h_magic, &C, &rest};
   return hipLaunchKernel(reinterpret_cast<const void*>(&replay_prep_kernel<OP, DK, TIN>),
                          dim3(unsigned(p.n) * unsigned(p.H)), dim3(256), args, 0, s);
 }
 
-template <int OP, int DK>
+template <int OP>
 hipError_t launch_finalize(const KParams& p, hipStream_t s) {
-  KParams arg = p;
-  void* args[] = {&arg};
-  return hipLaunchKernel(reinterpret_cast<const void*>(&finalize_kernel<OP, DK>),
-                         dim3(unsigned(p.n) * unsigned(p.H)), dim3(64), args, 0, s);
+  const int32_t* slots = p.slots;
+  int32_t* len = p.len;
+  int n = p.n, H = p.H, B = p.B, C = p.C;
+  uint32_t h_magic = 0xffffffffu / uint32_t(p.H);
+  void* args[] = {&slots, &len, &n, &H, &h_magic, &B, &C};
+  const unsigned total = unsigned(p.n) * unsigned(p.H);
+  return hipLaunchKernel(reinterpret_cast<const void*>(&finalize_kernel<OP>),
+                         dim3((total + 255) / 256), dim3(256), args, 0, s);
 }
 
+// Split replay with a log: [ReplayPrep and commit] -> tiles.  Otherwise: tiles ->
+// Finalize (with no log there is nothing to prepare, and the length stays 0).
 template <int OP, int DK, int DV, typename TIN>
 hipError_t launch_tiled_shape(int nv, bool split, const KParams& p, float* coef, hipStream_t s) {
   hipError_t e = hipSuccess;
-  if (split && p.C > 0) e = launch_prep<OP, DK, TIN>(p, coef, s);
+  split = split && p.C > 0;
+  if (split) e = launch_prep<OP, DK, TIN>(p, coef, s);
   if (e != hipSuccess) return e;
   if (nv == 2) e = split ? launch_tiled_one<OP, DK, DV, 2, true, TIN>(p, coef, s)
                          : launch_tiled_one<OP, DK, DV, 2, false, TIN>(p, coef, s);
   else if (nv == 4) e = split ? launch_tiled_one<OP, DK, DV, 4, true, TIN>(p, coef, s)
                               : launch_tiled_one<OP, DK, DV, 4, false, TIN>(p, coef, s);
   else return hipErrorInvalidValue;
-  if (e != hipSuccess) return e;
-  return launch_finalize<OP, DK>(p, s);
+  if (e != hipSuccess || split || p.C == 0) return e;
+  return launch_finalize<OP>(p, s);
 }
 
 template <int OP, typename TIN>
