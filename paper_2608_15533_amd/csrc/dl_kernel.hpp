@@ -360,10 +360,14 @@ struct Cfg {
   static constexpr int DL = OpTraits<OP>::PER_KEY ? DK : 1;   // log-decay width
   static constexpr int LPE = DK == DV ? 16 : 8;  // lanes per log entry (coefficient pass)
   static constexpr int RPL = DK / LPE;           // key rows per lane (coefficient pass)
-  static constexpr int EPP = NT / LPE < CE ? NT / LPE : CE;   // log entries per pass
+  // Log entries staged per merge chunk: the 64-entry build stages two chunks of 32 in
+  // turn (all 64 at once take LDS that leaves 64 x 64 heads four workgroups per CU: GLA
+  // 250x32 heads, bf16 state, M = 40: 34.2 us a step, in chunks 29.7).
+  static constexpr int CH = CE < 32 ? CE : 32;
+  static constexpr int EPP = NT / LPE < CH ? NT / LPE : CH;   // log entries per pass
   static constexpr int NP = CE / EPP;            // coefficient passes
   static constexpr int UQ = (CE + NRG - 1) / NRG;             // log-value quads per thread
-  static constexpr int KTS = CE + 4;             // LDS row stride of the decayed log keys
+  static constexpr int KTS = CH + 4;             // LDS row stride of the decayed log keys
   static constexpr bool DELTA = OpTraits<OP>::DELTA;
   static constexpr bool DECAY = OpTraits<OP>::DECAY;
   static constexpr bool BONUS = OpTraits<OP>::BONUS;
@@ -379,17 +383,19 @@ struct Cfg {
   // LDS floats of the cross-wave partial sums, and of the staged log values, which take
   // the same place once the sums are read.
   static constexpr int LRED = READS_OUT ? NW * 2 * DV : 0;
-  static constexpr int LU = MERGES_LOG ? CE * DV : 0;
+  static constexpr int LU = MERGES_LOG ? CH * DV : 0;
   static constexpr int LSCR = LRED > LU ? LRED : LU;
   // Registers over latency: the readout and coefficient loops are kept from running
-  // ahead of themselves (see pin), which fits 128 x 128 heads with long logs in three
-  // workgroups of 512 threads per CU.
-  static constexpr bool LEAN = NT == 512;
+  // ahead of themselves (see pin).  It fits 128 x 128 heads with long logs in three
+  // workgroups of 512 threads per CU, and the per-key snapshots of 64 entries in the
+  // registers of 256 (KDA 64x32 heads 128x64, M = 63: 35.6 us with spills, 25.9 without).
+  static constexpr bool LEAN = NT == 512 || (CE == 64 && OpTraits<OP>::PER_KEY);
   static_assert(NT % 64 == 0 && NT >= DK && NT >= DV, "a thread per key row and value column");
   static_assert(DK % NRG == 0 && RPT % 4 == 0, "whole blocks of four rows per thread");
   static_assert(64 % NCG == 0 && (NCG == 16 || NCG == 32), "a wave holds whole rows");
   static_assert(NT % LPE == 0 && (RPL == 4 || RPL == 8 || RPL == 16), "coefficient runs");
   static_assert(CE % EPP == 0 && EPP % (64 / LPE) == 0, "whole passes of whole waves");
+  static_assert(CE % CH == 0 && CH % EPP == 0, "a chunk is whole passes");
   static_assert(!(BONUS && DL == 1), "the bonus readout is only defined with per-key decay");
   // LDS position of key row r in the vectors the coefficient pass reads and in the
   // decayed log keys: the pass reads element x of every lane's run of RPL rows at once, so
@@ -399,8 +405,7 @@ struct Cfg {
 
 // Waves per SIMD the register allocator aims at: 4 (128 registers), and for the 512
 // threads of 17 to 32 log entries 6 (80), or 8 (64) with a bf16 state and bf16
-// activations.  More than 32 entries take LDS for two workgroups of 512 threads per CU in
-// any case.
+// activations.  With more than 32 entries the loaded log alone takes more.
 constexpr int waves_target(int dk, int dv, int ce, int state_bytes, int in_bytes) {
   return threads_per_head(dk, dv, ce) != 512 || ce > 32 ? 4
          : state_bytes == 2 && in_bytes == 2 ? 8 : 6;
@@ -440,7 +445,7 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
   __shared__ __align__(16) float s_scr[CF::LSCR];
   __shared__ __align__(16) float s_kt[CF::MERGES_LOG ? DK * KTS : 1];   // decayed log keys
   float* const s_red = s_scr;                     // [NW][2][DV] partial sums
-  float4* const s_u = reinterpret_cast<float4*>(s_scr);   // [CE][NCG] log values
+  float4* const s_u = reinterpret_cast<float4*>(s_scr);   // [CH][NCG] log values
 
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -625,12 +630,12 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
 
   // ---- 4. replay coefficients g_i(k), g_i(q) of the live entries ---------------------
   // A merging workgroup also writes the decayed keys K~_i[r] = e^(l'_r - Lam_i,r) K_i[r]
-  // to LDS here, from the same loads (the merge decay l' equals the readout decay, except
+  // of the first chunk to LDS here, from the same loads (the merge decay l' equals the readout decay, except
   // for RWKV6, which reads at ell), zeros past the live length.
   if constexpr (CF::REPLAYS) {
 #pragma unroll
     for (int a = 0; a < NP; ++a) {
-      const bool stage = CF::MERGES_LOG && merging;
+      const bool stage = CF::MERGES_LOG && merging && a * EPP < CF::CH;
       if (ew < EPP && (a * EPP + ew < L || stage)) {          // uniform per wave
         const int i = a * EPP + e_;
         const bool live = i < L;
@@ -764,40 +769,46 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
     constexpr bool kBvLds = CF::HAS_TOKEN && MODE != M_EAGER;
     if constexpr (kBvLds) __syncthreads();        // s_bv written, the partial sums read
     if constexpr (kBvLds) bv = *reinterpret_cast<const float4*>(&s_bv[4 * cg]);
-    if constexpr (CF::MERGES_LOG) {
-      if (L > 0) {                                // uniform
-        if constexpr (CF::REPLAYS) {              // log values from the replay's registers
+    // Stage chunk c0 of the log: values from the replay's registers, keys (the first
+    // chunk's are there already) from memory; a flush, which replays nothing, both from
+    // memory.  Zeros past the live length.
+    [[maybe_unused]] auto stage_chunk = [&](int c0) {
+      if (!CF::REPLAYS || c0 > 0) {
 #pragma unroll
-          for (int a = 0; a < UQ; ++a) {
-            const int i = a * NRG + rg;
-            if (i < CE) s_u[i * NCG + cg] = i < L ? u_raw[a].get() : f4(0.f);
-          }
-        } else {                                  // flush: keys and values from memory
+        for (int a = 0; a < CF::CH / EPP; ++a) {
+          if (ew < EPP) {
+            const int e = a * EPP + e_, i = c0 + e, ic = min(i, L - 1);
+            RawRun<TIN, RPL> kg;
+            RawRun<float, DL == 1 ? 4 : RPL> lg;
+            kg.load(Kb + size_t(ic) * DK + c_ * RPL);
+            float wt = 1.f;
+            if constexpr (DL != 1) lg.load(Lb + size_t(ic) * DK + c_ * RPL);
+            else if constexpr (CF::DECAY) wt = dl_exp(s_lm[0] - Lb[size_t(ic) * LS]);
 #pragma unroll
-          for (int a = 0; a < NP; ++a) {
-            if (ew < EPP) {
-              const int i = a * EPP + e_, ic = min(i, L - 1);
-              RawRun<TIN, RPL> kg;
-              RawRun<float, DL == 1 ? 4 : RPL> lg;
-              kg.load(Kb + size_t(ic) * DK + c_ * RPL);
-              float wt = 1.f;
-              if constexpr (DL != 1) lg.load(Lb + size_t(ic) * DK + c_ * RPL);
-              else if constexpr (CF::DECAY) wt = dl_exp(s_lm[0] - Lb[size_t(ic) * LS]);
-#pragma unroll
-              for (int x = 0; x < RPL; ++x) {
-                const int pr = x * LPE + c_;
-                if constexpr (DL != 1) wt = dl_exp(s_lm[pr] - lg.at(x));
-                s_kt[pr * KTS + i] = i < L ? wt * kg.at(x) : 0.f;
-              }
+            for (int x = 0; x < RPL; ++x) {
+              const int pr = x * LPE + c_;
+              if constexpr (DL != 1) wt = dl_exp(s_lm[pr] - lg.at(x));
+              s_kt[pr * KTS + e] = i < L ? wt * kg.at(x) : 0.f;
             }
           }
-          for (int x = tid; x < CE * NCG; x += NT) {
-            const int i = x / NCG;
-            s_u[x] = i < L ? ld4(Ub + size_t(i) * DV + 4 * (x % NCG)) : f4(0.f);
-          }
         }
-        __syncthreads();
       }
+      if constexpr (CF::REPLAYS) {
+#pragma unroll
+        for (int a = 0; a < UQ; ++a) {
+          const int i = a * NRG + rg, e = i - c0;
+          if (e >= 0 && e < CF::CH) s_u[e * NCG + cg] = i < L ? u_raw[a].get() : f4(0.f);
+        }
+      } else {
+        for (int x = tid; x < CF::CH * NCG; x += NT) {
+          const int i = c0 + x / NCG;
+          s_u[x] = i < L ? ld4(Ub + size_t(i) * DV + 4 * (x % NCG)) : f4(0.f);
+        }
+      }
+      __syncthreads();
+    };
+    if constexpr (CF::MERGES_LOG) {
+      if (L > 0) stage_chunk(0);                  // uniform
     }
     // The live length is written before the rows, so that no register is written behind
     // the state stores.
@@ -820,6 +831,7 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
     // reads another entry and the instruction broadcasts one block's (cbsz, abid).
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    static_assert(CE <= 2 * CF::CH, "at most two chunks");
     constexpr int NRB = RPT / 4, RBG = MODE == M_EAGER ? 1 : NRB < 2 ? NRB : 2, NR = 4 * RBG;
 #pragma unroll
     for (int g = 0; g < NRB; g += RBG) {
@@ -842,15 +854,21 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
             acc[rb][0][i] = r.x; acc[rb][1][i] = r.y; acc[rb][2][i] = r.z; acc[rb][3][i] = r.w;
           }
         }
+        static_assert(CE == CF::CH || RBG == NRB, "chunks are staged once");
         constexpr int EB = NCG / 4;               // entries per read of the A operand
         constexpr int CB = EB == 8 ? 3 : 2;       // cbsz: log2 of the blocks per broadcast
         for (int i0 = 0; i0 < L; i0 += EB) {      // zeros past the live length
+          if (CE > CF::CH && i0 == CF::CH) {      // the second chunk (one row group only)
+            __syncthreads();                      // the first is consumed
+            stage_chunk(i0);
+          }
+          const int e0 = CE > CF::CH && i0 >= CF::CH ? i0 - CF::CH : i0;
           float a[RBG];
 #pragma unroll
-          for (int rb = 0; rb < RBG; ++rb) a[rb] = s_kt[a_off[rb] + i0];
+          for (int rb = 0; rb < RBG; ++rb) a[rb] = s_kt[a_off[rb] + e0];
 #define DL_MERGE_ENTRY(e)                                                                   \
   {                                                                                         \
-    const float4 b = s_u[(i0 + e) * NCG + cg];                                              \
+    const float4 b = s_u[(e0 + e) * NCG + cg];                                              \
     _Pragma("unroll") for (int rb = 0; rb < RBG; ++rb) {                                    \
       acc[rb][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[rb], b.x, acc[rb][0], CB, e, 0);    \
       acc[rb][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[rb], b.y, acc[rb][1], CB, e, 0);    \
