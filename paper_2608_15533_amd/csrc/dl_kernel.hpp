@@ -344,15 +344,21 @@ struct UType { using type = std::conditional_t<OpTraits<OP>::DELTA, float, TIN>;
 // go, so a longer log takes more registers and its own build.
 constexpr int log_build(int capacity) { return capacity <= 16 ? 16 : capacity <= 32 ? 32 : 64; }
 
-// Threads per workgroup.
-constexpr int threads_per_head(int dk, int dv, int ce) {
-  return dk == 128 && dv == 128 && ce > 16 ? 512 : 256;
+// Threads per workgroup: 256, and 512 for 128 x 128 heads with more than 16 log entries
+// (see the top) and where 64 entries with per-key snapshots do not fit the registers of
+// 256: 128 x 64 heads with an fp32 state and fp32 activations (io_bytes, the two element
+// sizes together; KDA 64x24 heads, M = 48, us a step: 26.0 with 256, 21.7 with 512).
+template <int OP>
+constexpr int threads_per_head(int dk, int dv, int ce, int io_bytes) {
+  return dk == 128 && dv == 128 && ce > 16 ? 512
+         : dk == 128 && dv == 64 && ce == 64 && io_bytes == 8 && OpTraits<OP>::PER_KEY ? 512
+                                                                                      : 256;
 }
 
-template <int OP, int DK, int DV, int MODE, int CE_>
+template <int OP, int DK, int DV, int MODE, int CE_, int IO_BYTES>
 struct Cfg {
   static constexpr int CE = CE_;                 // log entries of the build (C <= CE)
-  static constexpr int NT = threads_per_head(DK, DV, CE);
+  static constexpr int NT = threads_per_head<OP>(DK, DV, CE, IO_BYTES);
   static constexpr int NCG = DV / 4;             // float4 column groups
   static constexpr int NRG = NT / NCG;           // row groups
   static constexpr int RPT = DK / NRG;           // state rows per thread
@@ -387,9 +393,9 @@ struct Cfg {
   static constexpr int LSCR = LRED > LU ? LRED : LU;
   // Registers over latency: the readout and coefficient loops are kept from running
   // ahead of themselves (see pin).  It fits 128 x 128 heads with long logs in three
-  // workgroups of 512 threads per CU, and the per-key snapshots of 64 entries in the
-  // registers of 256 (KDA 64x32 heads 128x64, M = 63: 35.6 us with spills, 25.9 without).
-  static constexpr bool LEAN = NT == 512 || (CE == 64 && OpTraits<OP>::PER_KEY);
+  // workgroups of 512 threads per CU, and 64 entries in the registers of 256 (KDA 64x32
+  // heads 128x64, M = 63: 35.6 us with spills, 25.9 without).
+  static constexpr bool LEAN = NT == 512 || CE == 64;
   static_assert(NT % 64 == 0 && NT >= DK && NT >= DV, "a thread per key row and value column");
   static_assert(DK % NRG == 0 && RPT % 4 == 0, "whole blocks of four rows per thread");
   static_assert(64 % NCG == 0 && (NCG == 16 || NCG == 32), "a wave holds whole rows");
@@ -405,10 +411,11 @@ struct Cfg {
 
 // Waves per SIMD the register allocator aims at: 4 (128 registers), and for the 512
 // threads of 17 to 32 log entries 6 (80), or 8 (64) with a bf16 state and bf16
-// activations.  With more than 32 entries the loaded log alone takes more.
-constexpr int waves_target(int dk, int dv, int ce, int state_bytes, int in_bytes) {
-  return threads_per_head(dk, dv, ce) != 512 || ce > 32 ? 4
-         : state_bytes == 2 && in_bytes == 2 ? 8 : 6;
+// activations.  With an fp32 state and fp32 activations, as with more than 32 entries,
+// the loaded log takes more (KDA 64x32 heads, M = 32, us a step: 47.0 at 6 with spills,
+// 34.4 at 4).
+constexpr int waves_target(int threads, int ce, int io_bytes) {
+  return threads != 512 || ce > 32 || io_bytes == 8 ? 4 : io_bytes == 4 ? 8 : 6;
 }
 
 // ------------------------------------------------------------------ the kernel
@@ -423,11 +430,14 @@ constexpr int waves_target(int dk, int dv, int ce, int state_bytes, int in_bytes
 // step in a captured graph): 64 heads 4.97 -> 4.03, 256 heads 6.31 -> 5.26, 2048 heads
 // 27.6 -> 25.9; RWKV6 64 x 64 with a bf16 state, 5120 heads: 15.4 -> 13.3.
 template <int OP, int DK, int DV, int MODE, typename TIN, typename TS, int CE>
-__global__ __launch_bounds__(threads_per_head(DK, DV, CE))
-__attribute__((amdgpu_waves_per_eu(waves_target(DK, DV, CE, int(sizeof(TS)), int(sizeof(TIN))))))
+__global__
+__launch_bounds__(threads_per_head<OP>(DK, DV, CE, int(sizeof(TIN) + sizeof(TS))))
+__attribute__((amdgpu_waves_per_eu(
+    waves_target(threads_per_head<OP>(DK, DV, CE, int(sizeof(TIN) + sizeof(TS))), CE,
+                 int(sizeof(TIN) + sizeof(TS))))))
 void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k_,
                      const void* q_, int H, uint32_t h_magic, int n, int C, KParams p) {
-  using CF = Cfg<OP, DK, DV, MODE, CE>;
+  using CF = Cfg<OP, DK, DV, MODE, CE, int(sizeof(TIN) + sizeof(TS))>;
   using TU = typename UType<OP, TIN>::type;
   constexpr int NT = CF::NT, NCG = CF::NCG, NRG = CF::NRG, RPT = CF::RPT, DL = CF::DL;
   constexpr int RPL = CF::RPL, LPE = CF::LPE, EPP = CF::EPP, NP = CF::NP, UQ = CF::UQ;
