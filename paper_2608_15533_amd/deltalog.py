@@ -222,8 +222,16 @@ class Token:
         self.struct = dl_token(_ptr(q), _ptr(k), _ptr(v), _ptr(beta), _ptr(lam), _ptr(u))
 
 
+# Handle of the current device's current stream without building the Stream object that
+# torch.cuda.current_stream() wraps around it: 2.8 -> 0.3 us of the 6.8 us a call took on
+# the host (a 4-slot dl_append_step; 4.6 us now, of which the launch is 2.5).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     return getattr(stream, "cuda_stream", stream)
 
