@@ -147,6 +147,19 @@ __device__ __forceinline__ float4 xor32_sum(float4 v) {
   return make_float4(xor32_sum(v.x), xor32_sum(v.y), xor32_sum(v.z), xor32_sum(v.w));
 }
 
+// Sums over lane pairs that leave each lane one of the two sums: a(l) + a(l ^ 32) in lanes
+// 0-31 and b(l) + b(l ^ 32) in lanes 32-63 (v_permlane32_swap trades a's upper half for
+// b's lower half), and likewise a in the even 16-lane rows and b in the odd ones.  One swap
+// and one addition do what two all-lane sums take two of each and two copies for.
+__device__ __forceinline__ float swap32_sum(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap16_sum(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Decay factors exp(x) for log-decay differences x <= 0: the hardware base-2
 // exponential of x * log2(e) (two instructions instead of the 13 of a correctly
 // rounded expf).  Its relative error is about 2^-24 * |x| * log2(e) plus one ulp
@@ -446,9 +459,9 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
   constexpr int GW = 64 / NCG;                    // row groups per wave
 
   __shared__ float s_kf[DK], s_qf[DK];            // k, q (coefficient-pass order)
-  __shared__ float2 s_x[DK];                      // e^(l_r) (k_r, q_r)
-  __shared__ float s_em[DK];                      // e^(l'_r)
-  __shared__ float s_lr[DL], s_lm[DL];            // l, l' (coefficient-pass order)
+  __shared__ float2 s_x[DK];                      // (k_r, q_r), times e^(l_r) per key
+  __shared__ float s_em[DL == 1 ? 1 : DK];        // e^(l'_r)              (per-key decay)
+  __shared__ float s_lr[DL], s_lm[DL];            // l, l' (coefficient-pass order; per key)
   __shared__ float s_gk[CE], s_gq[CE];            // replay coefficients
   __shared__ float s_dotw[WK];
   __shared__ __align__(16) float s_bv[DV];
@@ -575,38 +588,40 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
   const bool merging = MODE == M_MERGE || MODE == M_FLUSH || MODE == M_EAGER ||
                        (MODE == M_STEP && L == C);
 
-  // ---- 2. per-row decay factors (LDS) and the token dot product -----------------------
+  // ---- 2. decay factors and the token dot product -------------------------------------
+  // The cumulative log-decay equals the newest snapshot (Eq. 5 writes both with the same
+  // value) or 0 with an empty log.  Readouts are of the decayed state (the delta-rule
+  // correction, and the post-update output's base part), except RWKV6, which reads the
+  // old state; FLUSH and READOUT take the represented state as it stands.
+  //
+  // One decay per head scales whole sums, so every wave keeps it in a register (ell through
+  // the scalar path: entry L-1 is not written by this launch) and multiplies the base
+  // readout by it afterwards: neither the barrier below nor the readout waits for ell,
+  // which is known a memory round trip after the live length.  Per-key factors go into
+  // the vectors of the readout, in LDS.
+  float lm1 = 0.f, er1 = 1.f;                     // l' and e^l' (= e^l), one per head
+  if constexpr (DL == 1 && CF::DECAY) {
+    if constexpr (CF::HAS_LOG) {
+      if (L > 0) ell = scalar_ld(Lb + size_t(L - 1) * LS);
+    }
+    lm1 = ell + lam;
+    er1 = dl_exp(lm1);
+  }
   if (w < WK) {
-    // The cumulative log-decay equals the newest snapshot (Eq. 5 writes both with the
-    // same value) or 0 with an empty log.  Entry L-1 is not written by this launch, so
-    // one value per head is read through the scalar path.
-    if constexpr (CF::HAS_LOG && CF::DECAY) {
-      if (L > 0) {
-        if constexpr (DL == 1) ell = scalar_ld(Lb + size_t(L - 1) * LS);
-        else ell = Lb[size_t(L - 1) * LS + tid];
-      }
-    }
     const float kf = to_f32(k_raw), qf = to_f32(q_raw);
-    // Readouts of the decayed state (the delta-rule correction, and the post-update
-    // output's base part), except RWKV6, which reads the old state.
-    float lr, lm;
-    if constexpr (MODE == M_EAGER) {
-      lr = CF::BONUS ? 0.f : lam;
-      lm = lam;
-    } else if constexpr (MODE == M_STEP || MODE == M_MERGE) {
-      lm = ell + lam;
-      lr = CF::BONUS ? ell : lm;
-    } else {                        // FLUSH, READOUT: the represented state as it stands
-      lr = ell;
-      lm = ell;
-    }
-    const float er = dl_exp(lr);
     const int pr = CF::pos(tid);
     s_kf[pr] = kf;
     s_qf[pr] = qf;
-    s_x[tid] = make_float2(er * kf, er * qf);
-    s_em[tid] = dl_exp(lm);
-    if (tid < DL) {                               // DL == 1: tid == 0 == pr
+    if constexpr (DL == 1) {
+      s_x[tid] = make_float2(kf, qf);
+    } else {
+      if constexpr (CF::HAS_LOG) {
+        if (L > 0) ell = Lb[size_t(L - 1) * LS + tid];
+      }
+      const float lm = ell + lam, lr = CF::BONUS ? ell : lm;
+      const float er = dl_exp(lr);
+      s_x[tid] = make_float2(er * kf, er * qf);
+      s_em[tid] = dl_exp(lm);
       s_lr[pr] = lr;
       s_lm[pr] = lm;
     }
@@ -634,6 +649,10 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
         pin(ov);
       }
     }
+    if constexpr (DL == 1 && CF::DECAY) {
+      if constexpr (CF::NEEDS_C) cv = er1 * cv;
+      ov = er1 * ov;
+    }
     if constexpr (CF::NEEDS_C) pin(cv);
     pin(ov);
   }
@@ -650,7 +669,7 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
         const int i = a * EPP + e_;
         const bool live = i < L;
         float ak = 0.f, aq = 0.f, wt = 1.f;
-        if constexpr (DL == 1 && CF::DECAY) wt = live ? dl_exp(s_lr[0] - lr0[a]) : 0.f;
+        if constexpr (DL == 1 && CF::DECAY) wt = live ? dl_exp(lm1 - lr0[a]) : 0.f;
 #pragma unroll
         for (int x = 0; x < RPL; ++x) {
           const int pr = x * LPE + c_;
@@ -659,7 +678,7 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
           if constexpr (CF::NEEDS_C) ak = fmaf(kx, s_kf[pr], ak);
           aq = fmaf(kx, s_qf[pr], aq);
           if (DL != 1 && !CF::BONUS && stage) s_kt[pr * KTS + i] = live ? kx : 0.f;
-          if (CF::LEAN && x % 4 == 3) {
+          if (CF::LEAN && x % 2 == 1) {
             pin(ak);
             pin(aq);
           }
@@ -705,15 +724,21 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
   // ---- 6. sums over rows, update factors, output, append -----------------------------
   // Rows of one column group live in lanes NCG apart inside a wave, then across waves.
   if constexpr (CF::READS_OUT) {
-    if constexpr (NCG == 16) {
-      if constexpr (CF::NEEDS_C) cv = xor16_sum(cv);
-      ov = xor16_sum(ov);
-    }
-    if constexpr (CF::NEEDS_C) cv = xor32_sum(cv);
-    ov = xor32_sum(ov);
-    if ((tid & 63) < NCG) {
-      if constexpr (CF::NEEDS_C) st4(&s_red[w * 2 * DV + 4 * cg], cv);
-      st4(&s_red[(w * 2 + 1) * DV + 4 * cg], ov);
+    // The sums of a column group's lanes are left one part per lane (see swap32_sum), and
+    // each lane stores its part: c in lanes 0-31 and o in lanes 32-63, or halves of o.
+    const int lane = tid & 63, hi = lane >> 5, odd = (lane >> 4) & 1;
+    if constexpr (CF::NEEDS_C) {
+      const float4 v = make_float4(swap32_sum(cv.x, ov.x), swap32_sum(cv.y, ov.y),
+                                   swap32_sum(cv.z, ov.z), swap32_sum(cv.w, ov.w));
+      float* const d = &s_red[(w * 2 + hi) * DV + 4 * cg];
+      if constexpr (NCG == 32) st4(d, v);
+      else *reinterpret_cast<float2*>(d + 2 * odd) =
+          make_float2(swap16_sum(v.x, v.z), swap16_sum(v.y, v.w));
+    } else {
+      const float2 v = make_float2(swap32_sum(ov.x, ov.z), swap32_sum(ov.y, ov.w));
+      float* const d = &s_red[(w * 2 + 1) * DV + 4 * cg + 2 * hi];
+      if constexpr (NCG == 32) *reinterpret_cast<float2*>(d) = v;
+      else d[odd] = swap16_sum(v.x, v.y);
     }
     __syncthreads();
     float dot = 0.f;
@@ -766,7 +791,8 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
       if (w < WK) {
         static_cast<TIN*>(p.k_log)[(sh * size_t(C) + L) * DK + tid] = k_raw;
         if constexpr (CF::DECAY) {
-          if (tid < DL) Lb[size_t(L) * LS + tid] = s_lm[CF::pos(tid)];
+          if constexpr (DL != 1) Lb[size_t(L) * LS + tid] = s_lm[CF::pos(tid)];
+          else if (tid == 0) Lb[size_t(L) * LS] = lm1;
         }
         if (tid == 0) len[sh] = L + 1;
       }
@@ -793,7 +819,7 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
             kg.load(Kb + size_t(ic) * DK + c_ * RPL);
             float wt = 1.f;
             if constexpr (DL != 1) lg.load(Lb + size_t(ic) * DK + c_ * RPL);
-            else if constexpr (CF::DECAY) wt = dl_exp(s_lm[0] - Lb[size_t(ic) * LS]);
+            else if constexpr (CF::DECAY) wt = dl_exp(lm1 - Lb[size_t(ic) * LS]);
 #pragma unroll
             for (int x = 0; x < RPL; ++x) {
               const int pr = x * LPE + c_;
@@ -849,7 +875,8 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
 #pragma unroll
       for (int j = 0; j < NR; ++j) {
         const int r = rg + NRG * (4 * g + j);
-        m[j] = s_em[r] * t[4 * g + j].get();
+        const float em = DL == 1 ? er1 : s_em[DL == 1 ? 0 : r];
+        m[j] = em * t[4 * g + j].get();
         if constexpr (CF::HAS_TOKEN) m[j] = fma4(s_kf[CF::pos(r)], bv, m[j]);
       }
       if constexpr (CF::MERGES_LOG) {
