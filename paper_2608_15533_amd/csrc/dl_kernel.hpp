@@ -58,21 +58,10 @@ namespace dl {
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-__device__ __forceinline__ float ld1(const float* p) { return *p; }
-__device__ __forceinline__ float ld1(const uint16_t* p) { return __uint_as_float(uint32_t(*p) << 16); }
-
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 __device__ __forceinline__ float4 ld4(const uint16_t* p) {
   const uint2 w = *reinterpret_cast<const uint2*>(p);
   return make_float4(bf_lo(w.x), bf_hi(w.x), bf_lo(w.y), bf_hi(w.y));
-}
-
-// Copy four elements verbatim (bit-exact log entries).
-__device__ __forceinline__ void cp4(float* d, const float* s) {
-  *reinterpret_cast<float4*>(d) = *reinterpret_cast<const float4*>(s);
-}
-__device__ __forceinline__ void cp4(uint16_t* d, const uint16_t* s) {
-  *reinterpret_cast<uint2*>(d) = *reinterpret_cast<const uint2*>(s);
 }
 
 __device__ __forceinline__ void st4(float* d, float4 v) { *reinterpret_cast<float4*>(d) = v; }
@@ -92,17 +81,11 @@ __device__ __forceinline__ float4 fma4(float s, float4 b, float4 a) {
   return make_float4(fmaf(s, b.x, a.x), fmaf(s, b.y, a.y), fmaf(s, b.z, a.z), fmaf(s, b.w, a.w));
 }
 
-__device__ __forceinline__ float shfl_xor(float v, int m) { return __shfl_xor(v, m, 64); }
-
 // Sum over aligned groups of N lanes (N = 4, 8 or 16), every lane of a group ending with
-// the group's sum.  With DL_DPP_REDUCE the lane exchanges are DPP moves inside a 16-lane
-// row (mirror over 16 lanes, mirror over 8, then swaps of lane pairs of pairs and of lane
-// pairs), and the exchanges across rows below are the gfx950 row-swap instructions:
-// none needs an LDS round trip.  Otherwise all are xor shuffles.  Callers reduce only
-// where every lane of the wave is active.
-#ifndef DL_DPP_REDUCE
-#define DL_DPP_REDUCE 1
-#endif
+// the group's sum.  The lane exchanges are DPP moves inside a 16-lane row (mirror over 16
+// lanes, mirror over 8, then swaps of lane pairs of pairs and of lane pairs), and the
+// exchanges across rows below are the gfx950 row-swap instructions: none needs an LDS
+// round trip.  Callers reduce only where every lane of the wave is active.
 template <int CTRL>
 __device__ __forceinline__ float dpp_move(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
@@ -110,43 +93,12 @@ __device__ __forceinline__ float dpp_move(float v) {
 template <int N>
 __device__ __forceinline__ float group_sum(float v) {
   static_assert(N == 4 || N == 8 || N == 16, "DPP rows hold 16 lanes");
-  if constexpr (DL_DPP_REDUCE) {
-    if constexpr (N == 16) v += dpp_move<0x140>(v);   // row_mirror: lane i <- 15 - i
-    if constexpr (N >= 8) v += dpp_move<0x141>(v);    // row_half_mirror: lane i <- 7 - i
-    v += dpp_move<0x4E>(v);                           // quad_perm [2,3,0,1]
-    v += dpp_move<0xB1>(v);                           // quad_perm [1,0,3,2]
-  } else {
-#pragma unroll
-    for (int m = N / 2; m >= 1; m >>= 1) v += shfl_xor(v, m);
-  }
+  if constexpr (N == 16) v += dpp_move<0x140>(v);   // row_mirror: lane i <- 15 - i
+  if constexpr (N >= 8) v += dpp_move<0x141>(v);    // row_half_mirror: lane i <- 7 - i
+  v += dpp_move<0x4E>(v);                           // quad_perm [2,3,0,1]
+  v += dpp_move<0xB1>(v);                           // quad_perm [1,0,3,2]
   return v;
 }
-// v(lane) + v(lane ^ 16): v_permlane16_swap with both operands v hands each lane the two
-// values of its row pair.
-__device__ __forceinline__ float xor16_sum(float v) {
-  if constexpr (DL_DPP_REDUCE) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  } else {
-    return v + shfl_xor(v, 16);
-  }
-}
-// v(lane) + v(lane ^ 32), with v_permlane32_swap likewise.
-__device__ __forceinline__ float xor32_sum(float v) {
-  if constexpr (DL_DPP_REDUCE) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  } else {
-    return v + shfl_xor(v, 32);
-  }
-}
-__device__ __forceinline__ float4 xor16_sum(float4 v) {
-  return make_float4(xor16_sum(v.x), xor16_sum(v.y), xor16_sum(v.z), xor16_sum(v.w));
-}
-__device__ __forceinline__ float4 xor32_sum(float4 v) {
-  return make_float4(xor32_sum(v.x), xor32_sum(v.y), xor32_sum(v.z), xor32_sum(v.w));
-}
-
 // Sums over lane pairs that leave each lane one of the two sums: a(l) + a(l ^ 32) in lanes
 // 0-31 and b(l) + b(l ^ 32) in lanes 32-63 (v_permlane32_swap trades a's upper half for
 // b's lower half), and likewise a in the even 16-lane rows and b in the odd ones.  One swap
@@ -159,6 +111,9 @@ __device__ __forceinline__ float swap16_sum(float a, float b) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+// v(lane) + v(lane ^ 16) and v(lane) + v(lane ^ 32) in every lane.
+__device__ __forceinline__ float xor16_sum(float v) { return swap16_sum(v, v); }
+__device__ __forceinline__ float xor32_sum(float v) { return swap32_sum(v, v); }
 
 // Decay factors exp(x) for log-decay differences x <= 0: the hardware base-2
 // exponential of x * log2(e) (two instructions instead of the 13 of a correctly
@@ -302,21 +257,6 @@ template <int N> struct RawRun<uint16_t, N> {
     return x % 2 ? bf_hi(d) : bf_lo(d);
   }
 };
-
-// Lam_log addressing.  Per-key snapshots of a (slot, head) are contiguous rows of dk
-// values, [B,H,C,dk].  Scalar snapshots are stored entry-major, [B,C,H]: the H heads of a
-// slot append entry L side by side (one 128-byte line for 32 heads) instead of each
-// writing 4 bytes into a sector of its own.  Entry i of a (slot, head) is at
-// base[i * stride].
-template <int DL>
-__device__ __forceinline__ float* lam_log_base(const KParams& p, int slot, int h) {
-  if constexpr (DL == 1) return p.lam_log + size_t(slot) * size_t(p.C) * p.H + h;
-  else return p.lam_log + (size_t(slot) * p.H + h) * size_t(p.C) * DL;
-}
-template <int DL>
-__device__ __forceinline__ size_t lam_log_stride(const KParams& p) {
-  return DL == 1 ? size_t(p.H) : size_t(DL);
-}
 
 // Read one float at a workgroup-uniform address through the scalar path (the constant
 // address space): the read waits on its own counter instead of queueing behind the
@@ -539,14 +479,18 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
     else v_raw = (static_cast<const TIN*>(p.v) + th * DV)[cl];
     if constexpr (CF::DELTA) beta = scalar_ld(p.beta + th);
   }
-  const size_t LS = DL == 1 ? size_t(H) : size_t(DL);          // as lam_log_stride
+  // Per-key snapshots of a (slot, head) are contiguous rows of dk values, [B,H,C,dk].
+  // Scalar snapshots are entry-major, [B,C,H]: the H heads of a slot append entry L side by
+  // side (one 128-byte line for 32 heads) instead of each writing 4 bytes into a sector of
+  // its own.  Entry i of a (slot, head) is at Lb[i * LS].
+  const size_t LS = DL == 1 ? size_t(H) : size_t(DL);
   const TIN* Kb = nullptr;
   const TU* Ub = nullptr;
   float* Lb = nullptr;
   if constexpr (CF::HAS_LOG) {
     Kb = static_cast<const TIN*>(p.k_log) + sh * size_t(C) * DK;
     Ub = static_cast<const TU*>(p.u_log) + sh * size_t(C) * DV;
-    if constexpr (CF::DECAY)                                   // as lam_log_base
+    if constexpr (CF::DECAY)
       Lb = p.lam_log + (DL == 1 ? size_t(slot) * size_t(C) * H + h : sh * size_t(C) * DL);
     // The pointers' argument loads complete beside the live length's, not after it.
     asm volatile("" ::"s"(Kb), "s"(Ub), "s"(Lb));
