@@ -658,8 +658,11 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
       if (a * NRG + w * GW < L) {                 // uniform per wave
         const int i = a * NRG + rg, ic = min(i, L - 1);
         const float4 u = u_raw[a].get();
-        if constexpr (CF::NEEDS_C) cv = fma4(i < L ? s_gk[ic] : 0.f, u, cv);
-        ov = fma4(i < L ? s_gq[ic] : 0.f, u, ov);
+        const float gk = CF::NEEDS_C ? s_gk[ic] : 0.f, gq = s_gq[ic];
+        if (i < L) {                              // lanes past the log add nothing: entry L-1
+          if constexpr (CF::NEEDS_C) cv = fma4(gk, u, cv);   // may hold an infinity
+          ov = fma4(gq, u, ov);
+        }
       }
     }
   }

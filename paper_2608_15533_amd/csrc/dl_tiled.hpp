@@ -344,8 +344,10 @@ void tile_step_kernel(const int32_t* slots, const int32_t* len, void* S_, const 
         if constexpr (NEEDS_C) gk[a] = s_gk[ic];
         gq[a] = s_gq[ic];
       }
-      if constexpr (NEEDS_C) cv = fma4(i < L ? gk[a] : 0.f, u, cv);
-      ov = fma4(i < L ? gq[a] : 0.f, u, ov);
+      if (i < L) {                                 // as in the step kernel
+        if constexpr (NEEDS_C) cv = fma4(gk[a], u, cv);
+        ov = fma4(gq[a], u, ov);
+      }
     }
   }
   for (int i = UQ * NRG + rg; i < L; i += NRG) {   // entries past those loaded ahead
