@@ -184,8 +184,11 @@ int dl_readout(const dl_desc* desc, const dl_state* state, const void* q, float*
  * aligned, owned by the caller; required when split_replay != 0 and C > 0, ignored
  * otherwise.  Its contents are scratch: overwritten, never read across calls.  Calls
  * that share a workspace must not overlap.  If a later launch fails, DL_E_HIP is
- * returned and the earlier launch of the call may already be enqueued, so the state
- * must then be taken as partly stepped. */
+ * returned and the earlier launch of the call may already be enqueued.  With split replay
+ * one more launch then takes the committed lengths back, and the state is as before the
+ * call (if that launch fails too, the state must be taken as partly stepped); with fused
+ * replay the tiles have run and their lengths are not committed, and the state must be
+ * taken as partly stepped. */
 int dl_append_step_tiled(const dl_desc* desc, const dl_state* state, const dl_token* tok,
                          float* o, const int32_t* slots, int32_t n, int32_t value_tiles,
                          int32_t split_replay, void* workspace, size_t workspace_bytes,
@@ -204,7 +207,7 @@ int dl_tiled_workspace_bytes(const dl_desc* desc, int32_t n, size_t* bytes);
  * library holds in device memory, one per GPU, for the life of the process.  The caller
  * still passes the state, token and output buffers; the call allocates and frees
  * nothing and enqueues exactly the launches of dl_append_step_tiled(..., split_replay=1,
- * ...).
+ * ...), with the same state after a launch that fails.
  * The scratch needed is dl_tiled_workspace_bytes(desc, n); a call that needs more than
  * DL_NOALLOC_SCRATCH_BYTES returns DL_E_SCRATCH (after the argument checks, before any
  * HIP call) and enqueues nothing.

@@ -17,7 +17,8 @@
 // With split replay the length is committed ahead of the tiles: append maps L to L + 1 in
 // 1 .. C and merge maps C to 0, so every committed length has one L it came from and the
 // tiles read that (GDN 32x32 heads 128x128, M = 8, 4 tiles: the launch it saves is about
-// 4 us of the 23.5 us a step took with it).
+// 4 us of the 23.5 us a step took with it).  Where the tile launch is refused the commit is
+// taken back by a launch of its own, the same map the other way.
 //
 // The arithmetic per element is that of dl_kernel.hpp; the coefficient routine is shared
 // by the prepare kernel and the fused tile kernel, so the split and fused variants give
@@ -486,7 +487,8 @@ void tile_step_kernel(const int32_t* slots, const int32_t* len, void* S_, const 
 // ------------------------------------------------------------------ Finalize
 // One thread per (row, head): append -> L + 1; merge -> L = 0.  The cumulative log-decay
 // follows from Lam_log[L] (written by tile 0) and L, so L is all there is to commit.
-template <int OP>
+// BACK: the length before such a commit (the prepare kernel's, whose tiles did not run).
+template <int OP, bool BACK>
 __global__ __launch_bounds__(256) void finalize_kernel(const int32_t* slots, int32_t* len,
                                                        int n, int H, uint32_t h_magic,
                                                        int B, int C) {
@@ -499,7 +501,8 @@ __global__ __launch_bounds__(256) void finalize_kernel(const int32_t* slots, int
   const size_t sh = size_t(slot) * H + h;
   const int L = len[sh];
   if (L < 0 || L > C) return;                       // invalid: reported by the tiles
-  len[sh] = L < C ? L + 1 : 0;
+  if constexpr (BACK) len[sh] = L > 0 ? L - 1 : C;
+  else len[sh] = L < C ? L + 1 : 0;
 }
 
 // ------------------------------------------------------------------ dispatch
@@ -533,7 +536,7 @@ hipError_t launch_prep(const KParams& p, float* coef, hipStream_t s) {
                          dim3(unsigned(p.n) * unsigned(p.H)), dim3(256), args, 0, s);
 }
 
-template <int OP>
+template <int OP, bool BACK>
 hipError_t launch_finalize(const KParams& p, hipStream_t s) {
   const int32_t* slots = p.slots;
   int32_t* len = p.len;
@@ -541,7 +544,7 @@ hipError_t launch_finalize(const KParams& p, hipStream_t s) {
   uint32_t h_magic = 0xffffffffu / uint32_t(p.H);
   void* args[] = {&slots, &len, &n, &H, &h_magic, &B, &C};
   const unsigned total = unsigned(p.n) * unsigned(p.H);
-  return hipLaunchKernel(reinterpret_cast<const void*>(&finalize_kernel<OP>),
+  return hipLaunchKernel(reinterpret_cast<const void*>(&finalize_kernel<OP, BACK>),
                          dim3((total + 255) / 256), dim3(256), args, 0, s);
 }
 
@@ -557,9 +560,13 @@ hipError_t launch_tiled_shape(int nv, bool split, const KParams& p, float* coef,
                          : launch_tiled_one<OP, DK, DV, 2, false, TIN>(p, coef, s);
   else if (nv == 4) e = split ? launch_tiled_one<OP, DK, DV, 4, true, TIN>(p, coef, s)
                               : launch_tiled_one<OP, DK, DV, 4, false, TIN>(p, coef, s);
-  else return hipErrorInvalidValue;
-  if (e != hipSuccess || split || p.C == 0) return e;
-  return launch_finalize<OP>(p, s);
+  else e = hipErrorInvalidValue;
+  if (split) {
+    if (e != hipSuccess) (void)launch_finalize<OP, true>(p, s);   // e is what the caller hears
+    return e;
+  }
+  if (e != hipSuccess || p.C == 0) return e;
+  return launch_finalize<OP, false>(p, s);
 }
 
 template <int OP, typename TIN>
