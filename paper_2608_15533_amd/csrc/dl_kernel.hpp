@@ -23,12 +23,11 @@
 //   KDA 128x32 heads  M = 32: 67.9 / 59.7      KDA 64x32 heads   M = 64: 39.6 / 39.1
 //   RetNet 8x16 heads M = 64: 4.99 / 4.57      GLA 100x32, bf16 state, M = 64: 43.5 / 41.7
 //
-// Modes (one template per mode; the per-slot append/merge branch of Alg. 1 is taken
-// on the device from that slot's live length):
+// Modes (one template per mode; the per-slot append/merge branch of Alg. 1 is taken on the
+// device from that slot's live length; the flush has a kernel of its own, dl_flush.hpp):
 //   EAGER   Eq. 3 on a dense state (no log).
 //   STEP    Alg. 1: readout + replay, then append (Eq. 5) if L < C, else merge (Eq. 6).
 //   MERGE   the merge branch at the current L (a forced merge, any 0 <= L <= C).
-//   FLUSH   materialise Eq. 7 into the base and reset (no token).
 //   READOUT o = x^T (Eq. 7 state), no writes to the state.
 //
 // Per (slot, head) and step the arithmetic is (l' = ell + lambda):
@@ -332,16 +331,14 @@ struct Cfg {
   static constexpr bool BONUS = OpTraits<OP>::BONUS;
   static constexpr bool HAS_LOG = MODE != M_EAGER;
   static constexpr bool HAS_TOKEN = MODE == M_EAGER || MODE == M_STEP || MODE == M_MERGE;
-  static constexpr bool READS_OUT = MODE != M_FLUSH;
   static constexpr bool NEEDS_C = DELTA && HAS_TOKEN;
   static constexpr bool CAN_MERGE = MODE != M_READOUT;
   static constexpr bool MERGES_LOG = CAN_MERGE && HAS_LOG;
-  static constexpr bool REPLAYS = HAS_LOG && READS_OUT;   // readout of the live log
   // Waves of the per-row and the per-column work.
   static constexpr int WK = DK / 64, WV = DV / 64;
   // LDS floats of the cross-wave partial sums, and of the staged log values, which take
   // the same place once the sums are read.
-  static constexpr int LRED = READS_OUT ? NW * 2 * DV : 0;
+  static constexpr int LRED = NW * 2 * DV;
   static constexpr int LU = MERGES_LOG ? CH * DV : 0;
   static constexpr int LSCR = LRED > LU ? LRED : LU;
   // Registers over latency: the readout and coefficient loops are kept from running
@@ -369,6 +366,38 @@ struct Cfg {
 // 34.4 at 4).
 constexpr int waves_target(int threads, int ce, int io_bytes) {
   return threads != 512 || ce > 32 || io_bytes == 8 ? 4 : io_bytes == 4 ? 8 : 6;
+}
+
+// Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2).  Map
+// them so that each XCD owns whole chunks of DL_XCD_CHUNK consecutive (row, head)
+// pairs: the 4-byte per-head metadata (L and the head-wise log-decay snapshots) and token
+// scalars of a chunk then fill whole 128-byte lines in one L2 instead of being
+// written back partially by eight different caches.  Chunks are dealt to the XCDs
+// in turn, so a run of consecutive slots that merge in the same step (slots admitted
+// together) is spread over all eight XCDs instead of loading one of them.  Rows past
+// the last whole round of chunks keep the hardware order.
+__device__ __forceinline__ uint32_t xcd_chunked(uint32_t lin, uint32_t nblk) {
+  if constexpr (kXcdChunk > 0) {
+    const uint32_t full = nblk - nblk % (kXcds * kXcdChunk);
+    if (lin < full) {
+      const uint32_t x = lin % kXcds, j = lin / kXcds;
+      lin = ((j / kXcdChunk) * kXcds + x) * kXcdChunk + j % kXcdChunk;
+    }
+  } else if (nblk % kXcds == 0) {
+    lin = (lin % kXcds) * (nblk / kXcds) + lin / kXcds;   // one contiguous range per XCD
+  }
+  return lin;
+}
+
+// Token row lin / H and head lin % H.  h_magic = floor((2^32 - 1) / H) gives the
+// quotient or one less for any lin < 2^32.
+__device__ __forceinline__ void split_row(uint32_t lin, int H, uint32_t h_magic, int& row, int& h) {
+  row = int(__umulhi(lin, h_magic));
+  h = int(lin) - row * H;
+  if (h >= H) {
+    h -= H;
+    ++row;
+  }
 }
 
 // ------------------------------------------------------------------ the kernel
@@ -412,33 +441,8 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
 
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2).  Map
-  // them so that each XCD owns whole chunks of DL_XCD_CHUNK consecutive (row, head)
-  // pairs: the 4-byte per-head metadata (L and the head-wise log-decay snapshots) and token
-  // scalars of a chunk then fill whole 128-byte lines in one L2 instead of being
-  // written back partially by eight different caches.  Chunks are dealt to the XCDs
-  // in turn, so a run of consecutive slots that merge in the same step (slots admitted
-  // together) is spread over all eight XCDs instead of loading one of them.  Rows past
-  // the last whole round of chunks keep the hardware order.
-  uint32_t lin = blockIdx.x;
-  const uint32_t nblk = uint32_t(n) * uint32_t(H);
-  if constexpr (kXcdChunk > 0) {
-    const uint32_t full = nblk - nblk % (kXcds * kXcdChunk);
-    if (lin < full) {
-      const uint32_t x = lin % kXcds, j = lin / kXcds;
-      lin = ((j / kXcdChunk) * kXcds + x) * kXcdChunk + j % kXcdChunk;
-    }
-  } else if (nblk % kXcds == 0) {
-    lin = (lin % kXcds) * (nblk / kXcds) + lin / kXcds;   // one contiguous range per XCD
-  }
-  // Token row lin / H and head lin % H.  h_magic = floor((2^32 - 1) / H) gives the
-  // quotient or one less for any lin < 2^32.
-  int row = int(__umulhi(lin, h_magic));
-  int h = int(lin) - row * H;
-  if (h >= H) {
-    h -= H;
-    ++row;
-  }
+  int row, h;                                     // token row and head
+  split_row(xcd_chunked(blockIdx.x, uint32_t(n) * uint32_t(H)), H, h_magic, row, h);
   int slot = row;                                 // no list: the host has checked n <= B
   if (slots) {
     slot = slots[row];
@@ -460,7 +464,7 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
   Raw4<TIN> v4_raw{};
   float lam = 0.f, ell = 0.f, uf = 0.f, beta = 0.f;
   if constexpr (CF::HAS_TOKEN) k_raw = (static_cast<const TIN*>(k_) + th * DK)[rl];
-  if constexpr (CF::READS_OUT) q_raw = (static_cast<const TIN*>(q_) + th * DK)[rl];
+  q_raw = (static_cast<const TIN*>(q_) + th * DK)[rl];
   if constexpr (CF::HAS_TOKEN && CF::DECAY && DL != 1) lam = p.lam[th * DL + rl];
   sched_fence();
 
@@ -510,7 +514,7 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
   RawRun<float, DL == 1 ? 4 : RPL> lr_raw[NP];    // per-key snapshots (unused for DL == 1)
   float lr0[NP] = {};                             // scalar snapshots (DL == 1)
   Raw4<TU> u_raw[UQ];
-  if constexpr (CF::REPLAYS) {
+  if constexpr (CF::HAS_LOG) {
 #pragma unroll
     for (int a = 0; a < NP; ++a) {
       if (ew < EPP && a * EPP + ew < L) {         // uniform per wave
@@ -529,14 +533,13 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
   }
   sched_fence();
   // Does this (slot, head) materialise in this launch?  (Uniform per workgroup.)
-  const bool merging = MODE == M_MERGE || MODE == M_FLUSH || MODE == M_EAGER ||
-                       (MODE == M_STEP && L == C);
+  const bool merging = MODE == M_MERGE || MODE == M_EAGER || (MODE == M_STEP && L == C);
 
   // ---- 2. decay factors and the token dot product -------------------------------------
   // The cumulative log-decay equals the newest snapshot (Eq. 5 writes both with the same
   // value) or 0 with an empty log.  Readouts are of the decayed state (the delta-rule
   // correction, and the post-update output's base part), except RWKV6, which reads the
-  // old state; FLUSH and READOUT take the represented state as it stands.
+  // old state; READOUT takes the represented state as it stands.
   //
   // One decay per head scales whole sums, so every wave keeps it in a register (ell through
   // the scalar path: entry L-1 is not written by this launch) and multiplies the base
@@ -580,32 +583,30 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
 
   // ---- 3. base readout from the registers (the log entries may still be in flight) ------
   float4 cv = f4(0.f), ov = f4(0.f);
-  if constexpr (CF::READS_OUT) {
 #pragma unroll
-    for (int j = 0; j < RPT; ++j) {
-      const float2 x = s_x[rg + NRG * j];
-      const float4 sj = t[j].get();
-      if constexpr (CF::CAN_MERGE) t[j].opaque();
-      if constexpr (CF::NEEDS_C) cv = fma4(x.x, sj, cv);
-      ov = fma4(x.y, sj, ov);
-      if (CF::LEAN && j % 2 == 1) {
-        if constexpr (CF::NEEDS_C) pin(cv);
-        pin(ov);
-      }
+  for (int j = 0; j < RPT; ++j) {
+    const float2 x = s_x[rg + NRG * j];
+    const float4 sj = t[j].get();
+    if constexpr (CF::CAN_MERGE) t[j].opaque();
+    if constexpr (CF::NEEDS_C) cv = fma4(x.x, sj, cv);
+    ov = fma4(x.y, sj, ov);
+    if (CF::LEAN && j % 2 == 1) {
+      if constexpr (CF::NEEDS_C) pin(cv);
+      pin(ov);
     }
-    if constexpr (DL == 1 && CF::DECAY) {
-      if constexpr (CF::NEEDS_C) cv = er1 * cv;
-      ov = er1 * ov;
-    }
-    if constexpr (CF::NEEDS_C) pin(cv);
-    pin(ov);
   }
+  if constexpr (DL == 1 && CF::DECAY) {
+    if constexpr (CF::NEEDS_C) cv = er1 * cv;
+    ov = er1 * ov;
+  }
+  if constexpr (CF::NEEDS_C) pin(cv);
+  pin(ov);
 
   // ---- 4. replay coefficients g_i(k), g_i(q) of the live entries ---------------------
   // A merging workgroup also writes the decayed keys K~_i[r] = e^(l'_r - Lam_i,r) K_i[r]
   // of the first chunk to LDS here, from the same loads (the merge decay l' equals the readout decay, except
   // for RWKV6, which reads at ell), zeros past the live length.
-  if constexpr (CF::REPLAYS) {
+  if constexpr (CF::HAS_LOG) {
 #pragma unroll
     for (int a = 0; a < NP; ++a) {
       const bool stage = CF::MERGES_LOG && merging && a * EPP < CF::CH;
@@ -670,67 +671,65 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
   float4 bv = f4(0.f);
   // ---- 6. sums over rows, update factors, output, append -----------------------------
   // Rows of one column group live in lanes NCG apart inside a wave, then across waves.
-  if constexpr (CF::READS_OUT) {
-    // The sums of a column group's lanes are left one part per lane (see swap32_sum), and
-    // each lane stores its part: c in lanes 0-31 and o in lanes 32-63, or halves of o.
-    const int lane = tid & 63, hi = lane >> 5, odd = (lane >> 4) & 1;
-    if constexpr (CF::NEEDS_C) {
-      const float4 v = make_float4(swap32_sum(cv.x, ov.x), swap32_sum(cv.y, ov.y),
-                                   swap32_sum(cv.z, ov.z), swap32_sum(cv.w, ov.w));
-      float* const d = &s_red[(w * 2 + hi) * DV + 4 * cg];
-      if constexpr (NCG == 32) st4(d, v);
-      else *reinterpret_cast<float2*>(d + 2 * odd) =
-          make_float2(swap16_sum(v.x, v.z), swap16_sum(v.y, v.w));
-    } else {
-      const float2 v = make_float2(swap32_sum(ov.x, ov.z), swap32_sum(ov.y, ov.w));
-      float* const d = &s_red[(w * 2 + 1) * DV + 4 * cg + 2 * hi];
-      if constexpr (NCG == 32) *reinterpret_cast<float2*>(d) = v;
-      else d[odd] = swap16_sum(v.x, v.y);
+  // The sums of a column group's lanes are left one part per lane (see swap32_sum), and
+  // each lane stores its part: c in lanes 0-31 and o in lanes 32-63, or halves of o.
+  const int lane = tid & 63, hi = lane >> 5, odd = (lane >> 4) & 1;
+  if constexpr (CF::NEEDS_C) {
+    const float4 v = make_float4(swap32_sum(cv.x, ov.x), swap32_sum(cv.y, ov.y),
+                                 swap32_sum(cv.z, ov.z), swap32_sum(cv.w, ov.w));
+    float* const d = &s_red[(w * 2 + hi) * DV + 4 * cg];
+    if constexpr (NCG == 32) st4(d, v);
+    else *reinterpret_cast<float2*>(d + 2 * odd) =
+        make_float2(swap16_sum(v.x, v.z), swap16_sum(v.y, v.w));
+  } else {
+    const float2 v = make_float2(swap32_sum(ov.x, ov.z), swap32_sum(ov.y, ov.w));
+    float* const d = &s_red[(w * 2 + 1) * DV + 4 * cg + 2 * hi];
+    if constexpr (NCG == 32) *reinterpret_cast<float2*>(d) = v;
+    else d[odd] = swap16_sum(v.x, v.y);
+  }
+  __syncthreads();
+  float dot = 0.f;
+  if constexpr (CF::HAS_TOKEN) {
+#pragma unroll
+    for (int x = 0; x < WK; ++x) dot += s_dotw[x];
+  }
+  if constexpr (MODE == M_EAGER) {
+    // Every workgroup goes on to its update: each thread sums its own quad (in the same
+    // order), which saves a barrier and a trip through LDS.
+    cv = f4(0.f);
+    ov = f4(0.f);
+#pragma unroll
+    for (int x = 0; x < NW; ++x) {
+      if constexpr (CF::NEEDS_C) cv = cv + *reinterpret_cast<const float4*>(&s_red[x * 2 * DV + 4 * cg]);
+      ov = ov + *reinterpret_cast<const float4*>(&s_red[(x * 2 + 1) * DV + 4 * cg]);
     }
-    __syncthreads();
-    float dot = 0.f;
+    const float4 v = v4_raw.get();
+    bv = CF::DELTA ? beta * (v - cv) : v;
+    if (rg == 0) st4(p.o + th * DV + 4 * cg, fma4(dot, bv, ov));
+  } else if (w < WV) {
+    // One thread per value column (every thread summing its whole quad would read NRG
+    // times as much LDS as there are partial sums).
+    float c = 0.f, o = 0.f;
+#pragma unroll
+    for (int x = 0; x < NW; ++x) {
+      if constexpr (CF::NEEDS_C) c += s_red[x * 2 * DV + tid];
+      o += s_red[(x * 2 + 1) * DV + tid];
+    }
+    float b = 0.f;
     if constexpr (CF::HAS_TOKEN) {
-#pragma unroll
-      for (int x = 0; x < WK; ++x) dot += s_dotw[x];
+      const float v = to_f32(v_raw);
+      b = CF::DELTA ? beta * (v - c) : v;
+      o = fmaf(dot, b, o);                      // post-update readout, or the RWKV6 bonus
     }
-    if constexpr (MODE == M_EAGER) {
-      // Every workgroup goes on to its update: each thread sums its own quad (in the same
-      // order), which saves a barrier and a trip through LDS.
-      cv = f4(0.f);
-      ov = f4(0.f);
-#pragma unroll
-      for (int x = 0; x < NW; ++x) {
-        if constexpr (CF::NEEDS_C) cv = cv + *reinterpret_cast<const float4*>(&s_red[x * 2 * DV + 4 * cg]);
-        ov = ov + *reinterpret_cast<const float4*>(&s_red[(x * 2 + 1) * DV + 4 * cg]);
+    p.o[th * DV + tid] = o;
+    if constexpr (MODE == M_STEP) {
+      if (L < C) {                              // Eq. 5
+        TU* Ud = static_cast<TU*>(p.u_log) + (sh * size_t(C) + L) * DV;
+        if constexpr (CF::DELTA) reinterpret_cast<float*>(Ud)[tid] = b;
+        else Ud[tid] = v_raw;                   // bit-exact copy
       }
-      const float4 v = v4_raw.get();
-      bv = CF::DELTA ? beta * (v - cv) : v;
-      if (rg == 0) st4(p.o + th * DV + 4 * cg, fma4(dot, bv, ov));
-    } else if (w < WV) {
-      // One thread per value column (every thread summing its whole quad would read NRG
-      // times as much LDS as there are partial sums).
-      float c = 0.f, o = 0.f;
-#pragma unroll
-      for (int x = 0; x < NW; ++x) {
-        if constexpr (CF::NEEDS_C) c += s_red[x * 2 * DV + tid];
-        o += s_red[(x * 2 + 1) * DV + tid];
-      }
-      float b = 0.f;
-      if constexpr (CF::HAS_TOKEN) {
-        const float v = to_f32(v_raw);
-        b = CF::DELTA ? beta * (v - c) : v;
-        o = fmaf(dot, b, o);                      // post-update readout, or the RWKV6 bonus
-      }
-      p.o[th * DV + tid] = o;
-      if constexpr (MODE == M_STEP) {
-        if (L < C) {                              // Eq. 5
-          TU* Ud = static_cast<TU*>(p.u_log) + (sh * size_t(C) + L) * DV;
-          if constexpr (CF::DELTA) reinterpret_cast<float*>(Ud)[tid] = b;
-          else Ud[tid] = v_raw;                   // bit-exact copy
-        }
-      }
-      if constexpr (CF::CAN_MERGE) s_bv[tid] = b;
     }
+    if constexpr (CF::CAN_MERGE) s_bv[tid] = b;
   }
   if constexpr (MODE == M_READOUT) return;
   if constexpr (MODE == M_STEP) {
@@ -753,10 +752,9 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
     if constexpr (kBvLds) __syncthreads();        // s_bv written, the partial sums read
     if constexpr (kBvLds) bv = *reinterpret_cast<const float4*>(&s_bv[4 * cg]);
     // Stage chunk c0 of the log: values from the replay's registers, keys (the first
-    // chunk's are there already) from memory; a flush, which replays nothing, both from
-    // memory.  Zeros past the live length.
+    // chunk's are there already) from memory.  Zeros past the live length.
     [[maybe_unused]] auto stage_chunk = [&](int c0) {
-      if (!CF::REPLAYS || c0 > 0) {
+      if (c0 > 0) {
 #pragma unroll
         for (int a = 0; a < CF::CH / EPP; ++a) {
           if (ew < EPP) {
@@ -776,17 +774,10 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
           }
         }
       }
-      if constexpr (CF::REPLAYS) {
 #pragma unroll
-        for (int a = 0; a < UQ; ++a) {
-          const int i = a * NRG + rg, e = i - c0;
-          if (e >= 0 && e < CF::CH) s_u[e * NCG + cg] = i < L ? u_raw[a].get() : f4(0.f);
-        }
-      } else {
-        for (int x = tid; x < CF::CH * NCG; x += NT) {
-          const int i = c0 + x / NCG;
-          s_u[x] = i < L ? ld4(Ub + size_t(i) * DV + 4 * (x % NCG)) : f4(0.f);
-        }
+      for (int a = 0; a < UQ; ++a) {
+        const int i = a * NRG + rg, e = i - c0;
+        if (e >= 0 && e < CF::CH) s_u[e * NCG + cg] = i < L ? u_raw[a].get() : f4(0.f);
       }
       __syncthreads();
     };

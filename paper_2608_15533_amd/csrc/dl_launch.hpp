@@ -1,6 +1,7 @@
 // Template dispatch from runtime (mode, dk, dv, dtype) to a kernel instantiation.
 #pragma once
 
+#include "dl_flush.hpp"
 #include "dl_kernel.hpp"
 
 namespace dl {
@@ -22,6 +23,20 @@ hipError_t launch_build(const KParams& p, hipStream_t s) {
       block, args, 0, s);
 }
 
+template <int OP, int DK, int DV, typename TIN, typename TS>
+hipError_t launch_flush(const KParams& p, hipStream_t s) {
+  const int32_t* slots = p.slots;
+  int32_t* len = p.len;
+  void* S = p.S;
+  const void *k_log = p.k_log, *u_log = p.u_log;
+  int H = p.H, n = p.n, C = p.C;
+  uint32_t h_magic = 0xffffffffu / uint32_t(p.H);
+  KParams rest = p;
+  void* args[] = {&slots, &len, &S, &k_log, &u_log, &H, &h_magic, &n, &C, &rest};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&flush_kernel<OP, DK, DV, TIN, TS>),
+                         dim3(unsigned(p.n) * unsigned(p.H)), dim3(FlushCfg<DK, DV>::NT), args, 0, s);
+}
+
 // The build for the descriptor's log capacity (the eager kernel has no log).
 template <int OP, int DK, int DV, int MODE, typename TIN, typename TS>
 hipError_t launch_one(const KParams& p, hipStream_t s) {
@@ -38,7 +53,7 @@ hipError_t launch_mode(int mode, const KParams& p, hipStream_t s) {
     case M_EAGER: return launch_one<OP, DK, DV, M_EAGER, TIN, TS>(p, s);
     case M_STEP: return launch_one<OP, DK, DV, M_STEP, TIN, TS>(p, s);
     case M_MERGE: return launch_one<OP, DK, DV, M_MERGE, TIN, TS>(p, s);
-    case M_FLUSH: return launch_one<OP, DK, DV, M_FLUSH, TIN, TS>(p, s);
+    case M_FLUSH: return launch_flush<OP, DK, DV, TIN, TS>(p, s);
     case M_READOUT: return launch_one<OP, DK, DV, M_READOUT, TIN, TS>(p, s);
   }
   return hipErrorInvalidValue;

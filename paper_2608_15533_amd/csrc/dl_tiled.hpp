@@ -122,16 +122,6 @@ __device__ __forceinline__ float cumulative_decay(const float* Lb, size_t LS, in
   else return L > 0 ? Lb[size_t(L - 1) * LS + x] : 0.f;
 }
 
-// Token row and head of a linear index (see deltalog_kernel for h_magic).
-__device__ __forceinline__ void split_row(uint32_t lin, int H, uint32_t h_magic, int& row, int& h) {
-  row = int(__umulhi(lin, h_magic));
-  h = int(lin) - row * H;
-  if (h >= H) {
-    h -= H;
-    ++row;
-  }
-}
-
 // ------------------------------------------------------------------ ReplayPrep
 template <int OP, int DK, typename TIN>
 __global__ __launch_bounds__(256) void replay_prep_kernel(const int32_t* slots, int32_t* len,
@@ -219,15 +209,7 @@ void tile_step_kernel(const int32_t* slots, const int32_t* len, void* S_, const 
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   // Chunks of consecutive (row, head, tile) triples are dealt to the XCDs in turn (as in
   // the untiled kernel); a head's tiles sit in one chunk and share one L2.
-  uint32_t lin = blockIdx.x;
-  const uint32_t nblk = uint32_t(n) * uint32_t(H) * NV;
-  if constexpr (kXcdChunk > 0) {
-    const uint32_t full = nblk - nblk % (kXcds * kXcdChunk);
-    if (lin < full) {
-      const uint32_t x = lin % kXcds, jj = lin / kXcds;
-      lin = ((jj / kXcdChunk) * kXcds + x) * kXcdChunk + jj % kXcdChunk;
-    }
-  }
+  const uint32_t lin = xcd_chunked(blockIdx.x, uint32_t(n) * uint32_t(H) * NV);
   const int j = int(lin % NV);                     // value tile
   int row, h;
   split_row(lin / NV, H, h_magic, row, h);
