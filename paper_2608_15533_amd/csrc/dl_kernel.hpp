@@ -297,20 +297,15 @@ struct UType { using type = std::conditional_t<OpTraits<OP>::DELTA, float, TIN>;
 constexpr int log_build(int capacity) { return capacity <= 16 ? 16 : capacity <= 32 ? 32 : 64; }
 
 // Threads per workgroup: 256, and 512 for 128 x 128 heads with more than 16 log entries
-// (see the top) and where 64 entries with per-key snapshots do not fit the registers of
-// 256: 128 x 64 heads with an fp32 state and fp32 activations (io_bytes, the two element
-// sizes together; KDA 64x24 heads, M = 48, us a step: 26.0 with 256, 21.7 with 512).
-template <int OP>
-constexpr int threads_per_head(int dk, int dv, int ce, int io_bytes) {
-  return dk == 128 && dv == 128 && ce > 16 ? 512
-         : dk == 128 && dv == 64 && ce == 64 && io_bytes == 8 && OpTraits<OP>::PER_KEY ? 512
-                                                                                      : 256;
+// (see the top).
+constexpr int threads_per_head(int dk, int dv, int ce) {
+  return dk == 128 && dv == 128 && ce > 16 ? 512 : 256;
 }
 
-template <int OP, int DK, int DV, int MODE, int CE_, int IO_BYTES>
+template <int OP, int DK, int DV, int MODE, int CE_>
 struct Cfg {
   static constexpr int CE = CE_;                 // log entries of the build (C <= CE)
-  static constexpr int NT = threads_per_head<OP>(DK, DV, CE, IO_BYTES);
+  static constexpr int NT = threads_per_head(DK, DV, CE);
   static constexpr int NCG = DV / 4;             // float4 column groups
   static constexpr int NRG = NT / NCG;           // row groups
   static constexpr int RPT = DK / NRG;           // state rows per thread
@@ -359,13 +354,30 @@ struct Cfg {
   static __device__ __forceinline__ int pos(int r) { return (r % RPL) * LPE + r / RPL; }
 };
 
-// Waves per SIMD the register allocator aims at: 4 (128 registers), and for the 512
-// threads of 17 to 32 log entries 6 (80), or 8 (64) with a bf16 state and bf16
-// activations.  With an fp32 state and fp32 activations, as with more than 32 entries,
-// the loaded log takes more (KDA 64x32 heads, M = 32, us a step: 47.0 at 6 with spills,
-// 34.4 at 4).
-constexpr int waves_target(int threads, int ce, int io_bytes) {
-  return threads != 512 || ce > 32 || io_bytes == 8 ? 4 : io_bytes == 4 ? 8 : 6;
+// Waves per SIMD the register allocator aims at: 4 (128 registers; a kernel that needs fewer
+// takes fewer).
+//
+// The 512 threads of 17 to 32 log entries: 6 (80), or 8 (64) with a bf16 state and bf16
+// activations, which keeps two KDA merges from 81 and 65 registers; every other kernel of
+// them measures the same at 4, 6 and 8, but for spills: with fp32 state and activations at 6
+// (KDA 64x32 heads, M = 32, us a step: 47.0, 34.4 at 4), with bf16 activations and an fp32
+// state at 8 (KDA 48x32 heads, M = 18 to 33: 36.1, 21.4 at 6 and at 4).
+//
+// 64 entries in 256 threads of a rectangular head do not fit 128 registers where the
+// snapshots are per key and everything is fp32 in 128 x 64 heads (16 rows of a log entry a
+// lane), and in some merges with the token: 3 (168).  us a call, 1536 heads 128 x 64, all
+// fp32, steps of M = 33 to 64 (geometric mean): KDA 20.0 at 4 with spills, 18.6 with 512
+// threads, 17.7 at 3; GLA 18.3, 18.2, 17.3; RWKV6 19.8, 17.7, 16.9; at 40 heads KDA 4.9,
+// 4.4, 4.5.  dl_merge of KDA 64 x 128 heads, all fp32, M = 64: 34.7 at 4 with spills, 32.5
+// at 3.  Steps of 64 x 128 heads fit at 4 and are better there (KDA 15.5, at 3 15.8).
+template <int OP>
+constexpr int waves_target(int dk, int dv, int mode, int ce, int in_bytes, int state_bytes) {
+  const bool fp32 = in_bytes == 4 && state_bytes == 4, bf16 = in_bytes == 2 && state_bytes == 2;
+  if (threads_per_head(dk, dv, ce) == 512) return ce > 32 || fp32 ? 4 : bf16 ? 8 : 6;
+  if (ce == 64 && dk != dv &&
+      (mode == M_MERGE || (dk == 128 && fp32 && OpTraits<OP>::PER_KEY)))
+    return 3;
+  return 4;
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2).  Map
@@ -413,13 +425,12 @@ __device__ __forceinline__ void split_row(uint32_t lin, int H, uint32_t h_magic,
 // 27.6 -> 25.9; RWKV6 64 x 64 with a bf16 state, 5120 heads: 15.4 -> 13.3.
 template <int OP, int DK, int DV, int MODE, typename TIN, typename TS, int CE>
 __global__
-__launch_bounds__(threads_per_head<OP>(DK, DV, CE, int(sizeof(TIN) + sizeof(TS))))
+__launch_bounds__(threads_per_head(DK, DV, CE))
 __attribute__((amdgpu_waves_per_eu(
-    waves_target(threads_per_head<OP>(DK, DV, CE, int(sizeof(TIN) + sizeof(TS))), CE,
-                 int(sizeof(TIN) + sizeof(TS))))))
+    waves_target<OP>(DK, DV, MODE, CE, int(sizeof(TIN)), int(sizeof(TS))))))
 void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k_,
                      const void* q_, int H, uint32_t h_magic, int n, int C, KParams p) {
-  using CF = Cfg<OP, DK, DV, MODE, CE, int(sizeof(TIN) + sizeof(TS))>;
+  using CF = Cfg<OP, DK, DV, MODE, CE>;
   using TU = typename UType<OP, TIN>::type;
   constexpr int NT = CF::NT, NCG = CF::NCG, NRG = CF::NRG, RPT = CF::RPT, DL = CF::DL;
   constexpr int RPL = CF::RPL, LPE = CF::LPE, EPP = CF::EPP, NP = CF::NP, UQ = CF::UQ;

@@ -9,7 +9,7 @@ namespace dl {
 template <int OP, int DK, int DV, int MODE, typename TIN, typename TS, int CE>
 hipError_t launch_build(const KParams& p, hipStream_t s) {
   const dim3 grid(unsigned(p.n) * unsigned(p.H));
-  const dim3 block(threads_per_head<OP>(DK, DV, CE, int(sizeof(TIN) + sizeof(TS))));
+  const dim3 block(threads_per_head(DK, DV, CE));
   const int32_t* slots = p.slots;
   int32_t* len = p.len;
   void* S = p.S;
