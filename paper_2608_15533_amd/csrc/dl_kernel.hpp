@@ -477,6 +477,10 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
   if constexpr (CF::HAS_TOKEN) k_raw = (static_cast<const TIN*>(k_) + th * DK)[rl];
   q_raw = (static_cast<const TIN*>(q_) + th * DK)[rl];
   if constexpr (CF::HAS_TOKEN && CF::DECAY && DL != 1) lam = p.lam[th * DL + rl];
+  // An eager step has nothing else to do before its first barrier: the bonus, which the
+  // token dot product needs, goes ahead of the tile there (RWKV6 5x8 heads 128x128, bf16
+  // state: 4.42 -> 4.11 us).
+  if constexpr (CF::BONUS && MODE == M_EAGER) uf = p.u[size_t(h) * DK + rl];
   sched_fence();
 
   const int cg = tid % NCG, rg = tid / NCG;
@@ -489,7 +493,7 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
   for (int j = 0; j < RPT; ++j) t[j].load(srs, toff, j * kRowBlock);
   if constexpr (CF::HAS_TOKEN) {
     if constexpr (CF::DECAY && DL == 1) lam = scalar_ld(p.lam + th);
-    if constexpr (CF::BONUS) uf = p.u[size_t(h) * DK + rl];
+    if constexpr (CF::BONUS && MODE != M_EAGER) uf = p.u[size_t(h) * DK + rl];
     if constexpr (MODE == M_EAGER) v4_raw.load(static_cast<const TIN*>(p.v) + th * DV + 4 * cg);
     else v_raw = (static_cast<const TIN*>(p.v) + th * DV)[cl];
     if constexpr (CF::DELTA) beta = scalar_ld(p.beta + th);
@@ -593,12 +597,14 @@ void deltalog_kernel(const int32_t* slots, int32_t* len, void* S_, const void* k
   __syncthreads();
 
   // ---- 3. base readout from the registers (the log entries may still be in flight) ------
+  // bf16 rows are widened again for a merge, but kept by an eager step, which holds no log
+  // (RWKV6 5x8 heads 128x128: 4.66 -> 4.42 us; 128x32 heads 64x128 23.09 -> 23.01).
   float4 cv = f4(0.f), ov = f4(0.f);
 #pragma unroll
   for (int j = 0; j < RPT; ++j) {
     const float2 x = s_x[rg + NRG * j];
     const float4 sj = t[j].get();
-    if constexpr (CF::CAN_MERGE) t[j].opaque();
+    if constexpr (CF::CAN_MERGE && MODE != M_EAGER) t[j].opaque();
     if constexpr (CF::NEEDS_C) cv = fma4(x.x, sj, cv);
     ov = fma4(x.y, sj, ov);
     if (CF::LEAN && j % 2 == 1) {
