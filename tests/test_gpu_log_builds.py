@@ -1,6 +1,7 @@
-"""GPU tests of the step kernel's builds at the edges of their log capacities, for every
-head shape, activation dtype and state dtype, with an odd head count and slot lists that
-leave slots out: every output, merged base and the flushed base against the fp64 oracle."""
+"""GPU tests of the step kernel's builds at the edges of their log capacities (16, 32 and 64
+entries), each over several head shapes, activation and state dtypes and every build with a
+register target of its own, with an odd head count and slot lists that leave slots out:
+every output, merged base and the flushed base against the fp64 oracle."""
 
 import numpy as np
 import pytest
@@ -23,6 +24,10 @@ CASES = [  # op, dk, dv, capacity C, activations
     ("linattn", 128, 128, 32, "bf16"), ("linattn", 128, 128, 33, "f32"),
     ("retnet", 64, 128, 1, "bf16"), ("retnet", 128, 128, 33, "bf16"),
     ("gla", 128, 64, 17, "f32"), ("gla", 128, 128, 32, "bf16"), ("gla", 64, 64, 63, "bf16"),
+    # 64 entries in rectangular per-key heads: the register targets of their own
+    ("kda", 128, 64, 63, "f32"), ("kda", 128, 64, 63, "bf16"), ("kda", 64, 128, 63, "f32"),
+    ("gla", 128, 64, 33, "f32"), ("rwkv6", 128, 64, 63, "f32"),
+    ("kda", 64, 64, 33, "f32"), ("gdn", 128, 128, 63, "f32"), ("gdn", 128, 64, 32, "f32"),
 ]
 
 

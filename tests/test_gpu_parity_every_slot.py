@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 CASES = [
     ("gdn_b64_h32_d128_m16", W.GDN_B64, 16),
     ("kda_b128_h32_d128_m16", W.KDA_B128, 16),
-    ("kda_b128_h32_d128_m32", W.KDA_B128, 32),      # the long-log build (C > 16)
+    ("kda_b128_h32_d128_m32", W.KDA_B128, 32),      # the 32-entry build (C > 16)
     ("rwkv6_b128_h40_d64_m16", W.RWKV6_B128, 16),
     ("gla_b128_h32_d128_m16", W.GLA_B128, 16),
 ]

@@ -315,7 +315,7 @@ def test_bf16_state_head_shapes(op, dk, dv):
 
 @pytest.mark.parametrize("op", OPS)
 def test_largest_merge_interval(op):
-    """M = 64 (63 live entries, merged in 4 staged chunks) over 70 steps."""
+    """M = 64 (63 live entries, merged in two staged chunks) over 70 steps."""
     base = WL[op]
     w = base.with_(B=2, H=2, M=64, steps=70)
     S0 = W.initial_state(w)
