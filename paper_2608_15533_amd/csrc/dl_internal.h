@@ -53,7 +53,8 @@ hipError_t launch_retnet(int mode, int dk, int dv, bool bf16, bool state_bf16, c
 hipError_t launch_gla(int mode, int dk, int dv, bool bf16, bool state_bf16, const KParams& p,
                       hipStream_t s);
 
-// Value-tiled step (fp32 state): [ReplayPrep into coef when split] -> tiles -> Finalize.
+// Value-tiled step (fp32 state): [ReplayPrep into coef and commit] -> tiles when split,
+// else tiles -> [Finalize] (the bracketed launches only with a log).
 #define DL_DECLARE_TILED(name)                                                          \
   hipError_t launch_tiled_##name(int dk, int dv, bool bf16, int nv, bool split,          \
                                  const KParams& p, float* coef, hipStream_t s)

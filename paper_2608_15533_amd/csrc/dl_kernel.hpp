@@ -163,8 +163,9 @@ __device__ __forceinline__ uint32_t bf16_rne(float f) {
 }
 
 // Four consecutive state elements of one row, as held by one lane between the load and
-// the store.  fp32 state: one 16-byte access; bf16 state: one 8-byte access, widened to
-// fp32 on use and rounded (nearest even) on store.
+// the store.  fp32 state: one 16-byte access (stored by the kernels themselves, see the
+// merge); bf16 state: one 8-byte access, widened to fp32 on use and rounded (nearest even)
+// on store.
 template <typename TS> struct StateQuad;
 template <> struct StateQuad<float> {
   float4 w;
@@ -175,13 +176,6 @@ template <> struct StateQuad<float> {
   }
   __device__ __forceinline__ float4 get() const { return w; }
   __device__ __forceinline__ void opaque() {}
-  static __device__ __forceinline__ void store(__amdgpu_buffer_rsrc_t r, uint32_t voff,
-                                               uint32_t soff, float4 v) {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4 x = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z),
-                     __float_as_uint(v.w)};
-    __builtin_amdgcn_raw_buffer_store_b128(x, r, voff, soff, kStateStorePolicy);
-  }
 };
 template <> struct StateQuad<uint16_t> {
   uint2 w;
